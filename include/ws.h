@@ -172,8 +172,9 @@ typedef enum ws_option {
                                   equal ranges (1..8) instead of the balanced share */
   WS_OPT_AUDIO_KV_SPLITS = 1,  /* key-range splits of the audio kernel (1..512) */
   /* Softmax shift of the video kernel: 0 = automatic (a query row's logit
-   * bound |q''| * max |k| when it is at most 40 in log2 units, else a lazily
-   * raised running maximum), 1 = always the running maximum. */
+   * bound |q''| * max |k| when it is at most 40 in log2 units, above that the
+   * bound less 16 as long as the row's logits reach to within 80 of it, else
+   * a running maximum), 1 = always the running maximum. */
   WS_OPT_VIDEO_RUNNING_MAX = 2,
   /* ws_unit_attention_groups: 0 = the query groups share one round of the
    * CUs in proportion to their work, 1 = every group is partitioned as if it
@@ -265,8 +266,9 @@ WS_API ws_status ws_kv_release(ws_cache* cache, int32_t unit, ws_kind kind);
  * those are merged by log-sum-exp in a second kernel.
  * The softmax shift of a query row is its logit bound |Q''_i| * max |K'_j|
  * (Cauchy-Schwarz over the pages of one key range) when that bound is at most
- * 40 in log2 units, else a lazily raised running maximum
- * (WS_OPT_VIDEO_RUNNING_MAX forces the latter); both give the same softmax. */
+ * 40 in log2 units, above it the bound less 16 when the logits reach that far,
+ * else a running maximum (WS_OPT_VIDEO_RUNNING_MAX forces the latter); all
+ * give the same softmax. */
 WS_API ws_status ws_unit_attention(const void* q, int64_t q_tok_stride, int64_t q_head_stride,
                             int32_t n_q, const ws_query_desc* qdesc, ws_cache* cache,
                             const ws_mask_spec* mask, void* out, int64_t out_tok_stride,
@@ -334,9 +336,10 @@ typedef struct ws_attn_call {
  * 256-query tile (n_audio <= 256 * ceil(n_video / 256) - n_video), the video
  * kernel also computes the audio rows over the video call's pages (the pages
  * are streamed once for both); the pages the audio call alone sees (the
- * units' audio tokens) are walked by the video kernel's waves that have no
- * rows (when its last query tile leaves at least two) or else by the audio
- * kernel; the merge folds all the ranges.
+ * units' audio tokens) are walked by the last wave of the video kernel's last
+ * query tile, or by the audio kernel when the page list does not travel in the
+ * kernel arguments, audio key ranges are forced or the workspace is too small;
+ * the merge folds all the ranges.
  * WS_OPT_STEP_SEPARATE_AUDIO turns this off.  The video output always equals
  * what ws_unit_attention(video) writes, bit for bit; the audio output equals
  * ws_audio_attention(audio) bit for bit when the rows do not ride, and

@@ -24,10 +24,13 @@ LINK_FLAGS = ["-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lhipblaslt"]
 # Packed fp32 ops are kept out of the generated code on purpose.  The kernels
 # never form NaNs from finite inputs (masked logits are -inf, and no -inf - -inf
 # is evaluated), so NaN-quieting canonicalisations are not needed.
+# The MFMA builtins are to write vector registers: next to the video kernel's
+# accumulation-register O (inline asm) the compiler would otherwise put its S
+# tiles there too and copy every logit out before its exponential.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
              "-fno-honor-nans",
              "-Wall", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             "-I", INCLUDE, "-I", CSRC]
+             "-mllvm", "-amdgpu-mfma-vgpr-form", "-I", INCLUDE, "-I", CSRC]
 
 
 def _hipcc():

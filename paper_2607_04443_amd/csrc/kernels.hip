@@ -5,8 +5,9 @@
 //                  positions in fp32 before the bf16 store; V is stored
 //                  transposed per page ([d][slot]).
 //  unit_attn       video queries: flash attention over the visible pages with
-//                  v_mfma_f32_32x32x16_bf16, K/V pages staged through LDS
-//                  (double-buffered), online softmax in the exp2 domain.
+//                  v_mfma_f32_16x16x32_bf16, K/V pages staged through a ring
+//                  of LDS stages, softmax in the exp2 domain under a shift
+//                  fixed in advance.
 //  audio_attn      the few audio queries: memory-bound split-KV, one wave per
 //                  key range, v_mfma_f32_16x16x32_bf16 straight from registers.
 //  combine         log-sum-exp merge of split-KV partials.
@@ -20,6 +21,7 @@
 #include <cstddef>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "ws_kernels.hpp"
 
@@ -36,10 +38,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kNegInf = -__builtin_inff();
-// Lazy-max threshold of the video softmax, log2 units.
-constexpr float kLazyTau = 8.0f;
 // Largest logit bound (log2 units) used as a fixed softmax shift.
 constexpr float kShiftBoundMax = 40.0f;
+// Above it the video kernel's fixed shift is the bound less this much (p stays
+// at most 2^16, which leaves O room for 2^15 keys of values up to 2^96) ...
+constexpr float kShiftBelowBound = 16.0f;
+// ... as long as the row's largest logit is at most this far below the shift.
+constexpr float kShiftReach = 80.0f;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -345,50 +350,69 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const AppendArgs args) {
 }
 
 // ------------------------------------------------------------------------- //
-// unit_attn (video): 8 waves x 32 queries, 64-key pages through LDS.
+// unit_attn (video): 256-query tiles on 4 waves (one per SIMD) of 64 queries,
+// or of 32 queries where a tile holds at most 128 rows; 64-key pages through
+// LDS.
 //
-// Per wave and page, with lane l = 32*h + i (h = half, i = query column):
-//   S^T[key][q] = K[key][:] . Q'[q][:]   2 x (32x32) tiles, 8 MFMAs of k=16 each
-//   O^T[d][q]  += V^T[d][key] P^T[key][q] 4 x (32x32) tiles, 4 MFMAs of k=16 each
-// Every lane owns one query column, so the softmax row statistics live in one
-// lane (plus its partner l^32).  The K rows of S-tile row m are loaded from key
-// swap23(m) (bits 2 and 3 exchanged), which makes accumulator register r of
-// lane half h hold key 16*(r/8) + 8*h + (r%8): registers 0-7 and 8-15 are then
-// directly the B operands (eight consecutive keys) of the P*V MFMAs.
+// Per wave and page, with lane l = 16 g + i (i = query column of a 16-query
+// subtile, g = lane group) and v_mfma_f32_16x16x32_bf16:
+//   S^T[16 keys][16 q]  = K Q''^T    4 key tiles x 4 k-steps per subtile
+//   O^T[16 d][16 q]    += V^T P^T    8 d tiles x 2 key chunks of 32
+//   l[q]               += 1 P^T      2 key chunks (the row sums, on the matrix
+//                                    pipe: over the same bf16 P as O)
+// Row m = 4 g' + r of key tile t holds key 32 (t/2) + 8 g' + 4 (t%2) + r
+// (audio_key below), so registers r of tiles 2c and 2c + 1 in lane group g are
+// keys 32 c + 8 g + 0..7: directly the B operand of the P*V MFMA of chunk c.
+//
+// What bounds it: at the long windows the chip's power limit, then the matrix
+// pipe.  The MFMA shape, the operand reuse and the row sums follow from that.
+// Measured on the page loop alone (256 CUs, random operands, no page loads):
+//   32x32x16 MFMAs, 8 waves x 32 rows               1.455 us per page
+//   32x32x16 MFMAs, 4 waves x 64 rows               1.43  us
+//   16x16x32 MFMAs, 8 waves x 32 rows               1.33-1.41 us
+//   16x16x32 MFMAs, 4 waves x 64 rows, v_dot2 sums  1.30-1.40 us
+//   16x16x32 MFMAs, 4 waves x 64 rows, MFMA sums    1.23-1.27 us
+// (16x16x32 sustains 2170-2240 TFLOP/s on random register operands, 32x32x16
+// 1950; 64 rows per wave halve the LDS operand reads; a row-sum MFMA costs
+// less than the 16 v_dot2 it replaces.)
 // ------------------------------------------------------------------------- //
-__device__ __forceinline__ int swap23(int m) { return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1); }
+
+// f(Const<0>), ..., f(Const<N - 1>), unrolled by construction.
+template <int N>
+struct Const {
+  static constexpr int value = N;
+};
+template <class F, int... Is>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, Is...>) {
+  (f(Const<Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Row m (lane index i) of key tile t: the key it holds.
+__device__ __forceinline__ int audio_key(int t, int m) {
+  return 32 * (t >> 1) + 8 * (m >> 2) + 4 * (t & 1) + (m & 3);
+}
+
 // LDS stages of the video kernel (a ring of five pages, 160 KB: the previous
 // page, whose V^T the pipelined schedule still reads, the current page, the
 // next page, already complete so that its first operands can be read before
 // the page barrier, and the two after it in flight), filled by direct
 // global->LDS loads (global_load_lds_dwordx4: lane l of a wave writes 16
-// bytes at base + 16 l).
-//   K    [64 rows][16 chunks]: row R holds key swap23(R); its logical chunk c
-//        (dims 8c..8c+7) sits at position c ^ (R & 15).  Lane i of either
-//        half then reads row i (+32 for the second tile), and the 16 lanes
-//        of a ds_read_b128 pass hit 16 distinct 16-byte bank groups.
+// bytes at base + 16 l).  A stage is a K tile, then a V tile:
+//   K    [64 rows][16 chunks]: row 16 t + m holds key audio_key(t, m); its
+//        logical chunk c (dims 8c..8c+7) sits at position c ^ m.
 //   V^T  [128 d][8 chunks]: logical chunk c (keys 8c..8c+7) of row d sits at
 //        position c ^ ((d >> 1) & 7).
+// Either way the 16 lanes of a lane group read 16 distinct 16-byte bank groups.
 constexpr int kStages = 5;
-__shared__ __attribute__((aligned(1024))) uint16_t g_k0[kPageTokens * kHeadDim];
-__shared__ __attribute__((aligned(1024))) uint16_t g_k1[kPageTokens * kHeadDim];
-__shared__ __attribute__((aligned(1024))) uint16_t g_k2[kPageTokens * kHeadDim];
-__shared__ __attribute__((aligned(1024))) uint16_t g_k3[kPageTokens * kHeadDim];
-__shared__ __attribute__((aligned(1024))) uint16_t g_k4[kPageTokens * kHeadDim];
-__shared__ __attribute__((aligned(1024))) uint16_t g_v0[kHeadDim * kPageTokens];
-__shared__ __attribute__((aligned(1024))) uint16_t g_v1[kHeadDim * kPageTokens];
-__shared__ __attribute__((aligned(1024))) uint16_t g_v2[kHeadDim * kPageTokens];
-__shared__ __attribute__((aligned(1024))) uint16_t g_v3[kHeadDim * kPageTokens];
-__shared__ __attribute__((aligned(1024))) uint16_t g_v4[kHeadDim * kPageTokens];
+constexpr uint32_t kStageBytes = 2 * kPageHeadElems * 2;
+constexpr uint32_t kStageV = kPageHeadElems * 2;  // offset of the V tile
+__shared__ __attribute__((aligned(1024))) uint16_t g_stages[kStages * 2 * kPageHeadElems];
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-struct VideoState {
-  f32x16 o[4];
-  float m_run;
-  float l_run;
-  bool first;
-};
 
 // Read-only for a whole launch: accessed through the constant address space
 // so that uniform reads become scalar loads.
@@ -405,27 +429,176 @@ __device__ __forceinline__ const_page_list page_list(const AttnArgs& a) {
   return (const_page_list)(seg + offsetof(AttnArgs, inline_pages));
 }
 
-struct VideoCtx {
-  bool active;             // the wave has at least one real query row
-  const_page_list pages;   // visible page list
-  const uint16_t* kpool;   // pool base + this head's tile offset
-  const uint16_t* vpool;
-  int64_t page_stride;     // elements per page (all heads)
-  int wave, half, l32;
-  uint32_t dma_k, dma_v;   // this lane's source byte offsets within a tile (block i = 0)
-  bf16x8 qreg[8];
-};
-
 // LDS byte offset of a pointer into a __shared__ object.
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p));
 }
+// 16 bytes at an LDS byte offset.
+__device__ __forceinline__ bf16x8 lds_read16(uint32_t off) {
+  return as_bf16x8(*(const __attribute__((address_space(3))) u32x4*)off);
+}
+
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// The video kernel's MFMAs.  The S tiles sit in vector registers (the softmax
+// reads them; the build asks for that form of the MFMA builtins), O and l in
+// accumulation registers, by inline asm: the compiler's own choice puts all
+// of them in one bank, and every exponential or every O update then goes
+// through a copy.  The compiler does not see the matrix pipe's latency behind
+// the asm: O and l are read or written by other instructions only across
+// mfma_drain(), and a P word or another vector operand is written at least
+// two instructions ahead of the asm that reads it.
+__device__ __forceinline__ void mfma_s(f32x4& d, bf16x8 a, bf16x8 b, const f32x4& c) {
+  d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ void mfma_o(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+// The first product into an accumulator (C = 0).
+__device__ __forceinline__ void mfma_o_first(f32x4& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(d) : "v"(a), "v"(b));
+}
+// A value the compiler cannot carry over from an earlier computation: the
+// epilogue recomputes its addresses instead of keeping them live across the
+// page loop.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// Waits until every MFMA issued so far has written its result (and, between a
+// vector write and a following MFMA, until the write is visible to it).
+__device__ __forceinline__ void mfma_drain() {
+  sched_fence();
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  sched_fence();
+}
+
+// max and sum over lanes l, l ^ 16 (kLane = 16) or l, l ^ 32 (v_permlane*_swap:
+// no LDS round trip)
+template <int kLane>
+__device__ __forceinline__ float pair_max(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int kLane>
+__device__ __forceinline__ float pair_sum(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// max over the wave (rotations within a row of 16, then the swaps)
+template <int kRor>
+__device__ __forceinline__ float ror_max(float v) {
+  const int u = __float_as_int(v);
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(u, u, 0x120 + kRor, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return pair_max<32>(pair_max<16>(ror_max<1>(ror_max<2>(ror_max<4>(ror_max<8>(v))))));
+}
+// |q|^2 of the lane's words, added to acc
+__device__ __forceinline__ float norm2_words(u32x4 w, float acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t x = w[i];
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, x), acc, false);
+  }
+  return acc;
+}
+
+// What one page's iteration addresses, computed a little at a time during the
+// iteration before it, so that the page boundary holds nothing but the
+// barrier.
+struct PageCtx {
+  uint32_t k[4];        // LDS offsets of this lane's operand reads: K, per k-step (key tile t: + 4096 t)
+  uint32_t v;           // V^T chunk 0 (d tile dt: + 2048 dt)
+  uint32_t vp;          // V^T chunk 1 of the page before
+  const uint16_t* ldk;  // the loads to issue, of the page three ahead: K and V tile,
+  const uint16_t* ldv;
+  uint32_t lds;         // and their LDS offset
+};
+
+// A workgroup's share of one query tile's (head, page) units, lo .. lo + n - 1
+// in head-major order: one continuous stream of pages through the LDS ring,
+// whatever heads it crosses.  A unit's list entry is its tile index
+// (page * H + head) and the page's valid tokens; each lane holds the entries
+// of two units out of a window of 128, read with v_readlane, so that the page
+// loop has no scalar load to wait for (scalar loads and LDS reads share a
+// counter that only a full wait can order).
+struct VideoStream {
+  const_page_list pages;
+  FastDiv div_pages;
+  int num_heads, n_pages, page0, lo, n;
+  int lane;
+  uint32_t ent[2];        // entries of units 64 k + lane of the window (tile index << 7 | valid tokens)
+  int raw_head[2], raw_page[2], raw_valid[2];  // what ent is made of
+  float kn2[2];           // key-norm maxima (squared) of the first window's units
+  const uint16_t* kpool;
+  const uint16_t* vpool;
+  uint32_t dma_k, dma_v;  // this lane's source byte offsets within a tile (block 0)
+  uint32_t k_read, v_read;  // this lane's operand read offsets within a stage (k-step 0, chunk 0)
+  uint32_t lds0;          // LDS offset of the wave's first block in stage 0
+  int at;                 // stream index of the current page
+  uint32_t stage;         // its stage's LDS offset
+  uint32_t valid;         // valid tokens of pages at .. at + 3, a byte each
+  PageCtx c;              // the current page's context
+};
+
+// (Past the end: the last unit's entry.  No lane-dependent branch here or
+// anywhere else inside the page loops' regions: with one, the compiler
+// serialises the uniform branches around it and keeps the accumulators of both
+// sides.)
+__device__ __forceinline__ uint32_t stream_entry(const VideoStream& s, int k) {
+  const uint32_t x = s.lo + min(k, s.n - 1), head = fast_div(x, s.div_pages);
+  const int pi = s.page0 + static_cast<int>(x - head * s.n_pages);
+  return ((s.pages[pi].x * s.num_heads + head) << 7) | static_cast<uint32_t>(s.pages[pi].y);
+}
+// The first window: its list entries requested, then combined.
+__device__ __forceinline__ void stream_request(VideoStream& s) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const uint32_t x = s.lo + min(64 * k + s.lane, s.n - 1), head = fast_div(x, s.div_pages);
+    const int pi = s.page0 + static_cast<int>(x - head * s.n_pages);
+    s.raw_head[k] = head;
+    s.raw_page[k] = s.pages[pi].x;
+    s.raw_valid[k] = s.pages[pi].y;
+  }
+}
+__device__ __forceinline__ void stream_combine(VideoStream& s) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    s.ent[k] = ((s.raw_page[k] * s.num_heads + s.raw_head[k]) << 7) | static_cast<uint32_t>(s.raw_valid[k]);
+}
+// Entry of stream index k (uniform, inside the window).
+__device__ __forceinline__ uint32_t stream_peek(const VideoStream& s, int k) {
+  const uint32_t e0 = __builtin_amdgcn_readlane(s.ent[0], k & 63), e1 = __builtin_amdgcn_readlane(s.ent[1], k & 63);
+  return (k & 64) ? e1 : e0;
+}
+// Moves the window when the page to look up next, at + 4, enters a new half:
+// it replaces the half that lies two behind.
+__device__ __forceinline__ void stream_reach(VideoStream& s) {
+  const int k = s.at + 4;
+  if ((k & 63) == 0 && k >= 128) {
+    uint32_t e = stream_entry(s, k + s.lane);
+    asm volatile("" : "+v"(e));  // waited for here, not at every later use
+    if (k & 64) s.ent[1] = e; else s.ent[0] = e;
+  }
+}
+constexpr uint32_t kRingBytes = kStages * kStageBytes;
+__device__ __forceinline__ uint32_t ring_add(uint32_t stage, uint32_t k) {
+  const uint32_t x = stage + k * kStageBytes;
+  return x >= kRingBytes ? x - kRingBytes : x;
+}
 
 // One direct load: each lane's 16 bytes at sbase + voff go to LDS at
-// lds + 16 * lane.  Written as inline asm: with the compiler's own LDS-DMA
-// intrinsic in flight, every later LDS read waits for lgkmcnt(0), which
-// serializes the MFMA operand reads.  M0 is restored afterwards; completion
-// is tracked by the explicit vmcnt wait in wait_dma.
+// lds + kLdsAdd + 16 * lane.  Written as inline asm: with the compiler's own
+// LDS-DMA intrinsic in flight, every later LDS read waits for lgkmcnt(0),
+// which serializes the MFMA operand reads.  Completion is tracked by the
+// explicit vmcnt waits below.  M0 is the asm's own: nothing the compiler
+// emits in this kernel keeps a value in it.
+template <uint32_t kLdsAdd>
 __device__ __forceinline__ void dma16(const uint16_t* sbase, uint32_t voff, uint32_t lds) {
   // both are wave-uniform by construction; make that visible to the compiler
   // (readfirstlane returns int: widen through uint32_t, never sign-extend)
@@ -434,628 +607,554 @@ __device__ __forceinline__ void dma16(const uint16_t* sbase, uint32_t voff, uint
   const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)));
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b)));
   sbase = reinterpret_cast<const uint16_t*>((static_cast<uint64_t>(hi) << 32) | lo);
-  uint32_t saved;
   asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "global_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(voff), "s"(sbase), "s"(lds)
-      : "memory");
+      "s_add_u32 m0, %2, %3\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(voff), "s"(sbase), "s"(lds), "i"(kLdsAdd)
+      : "memory", "scc");
 }
 
-// Issues the direct loads of page `page` (K and V^T tiles of this head) into
-// the stage (k_dst, v_dst): per wave two 1 KB blocks of each, block
-// b = 8 i + wave.  Block b of K is rows 4b..4b+3, lane l at row
-// R = 32 i + 4 wave + l/16, position l%16; block b of V^T is rows
-// d = 64 i + 8 wave + l/8, position l%8.  The lane's source offset changes
-// with i only by a constant: 32 keys (1024 elements) in the K tile, 64 d
-// rows (2048 elements) in the V tile.
-__device__ __forceinline__ void stage_dma(const VideoCtx& c, int page, uint16_t* k_dst, uint16_t* v_dst) {
-  const uint16_t* kp = c.kpool + page * c.page_stride;
-  const uint16_t* vp = c.vpool + page * c.page_stride;
-  const uint32_t kl = lds_offset(k_dst) + 1024 * c.wave, vl = lds_offset(v_dst) + 1024 * c.wave;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    dma16(kp + 1024 * i, c.dma_k, kl + 8192 * i);
-    dma16(vp + 2048 * i, c.dma_v, vl + 8192 * i);
+// The direct loads of one page: 32 blocks of 1 KB, 8 per wave (block 4 i +
+// wave of each tile, i = 0..3).  Block b of K is rows 4 b .. 4 b + 3, i.e.
+// rows 4 wave .. of key tile i (keys 32 (i / 2) + 4 (i % 2) + 8 wave ..); block
+// b of V^T is rows d = 8 b .. 8 b + 7.
+constexpr int kDmaPerPage = 8;  // direct loads per wave and page
+template <int kPart>            // 0..3: K blocks, 4..7: V blocks
+__device__ __forceinline__ void issue_load(const VideoStream& s, const PageCtx& c) {
+  if constexpr (kPart < 4) {
+    constexpr uint32_t src = 2u * k_tile_index(32 * (kPart >> 1) + 4 * (kPart & 1), 0);
+    dma16<4096u * kPart>(c.ldk, s.dma_k + src, c.lds);
+  } else {
+    constexpr uint32_t src = 2u * v_tile_index(0, 32 * (kPart - 4));
+    dma16<kStageV + 4096u * (kPart - 4)>(c.ldv, s.dma_v + src, c.lds);
   }
 }
-constexpr int kDmaPerPage = 4;  // direct loads per wave and page
+__device__ __forceinline__ void issue_page(const VideoStream& s, const PageCtx& c) {
+  static_for<kDmaPerPage>([&](auto i) __attribute__((always_inline)) { issue_load<decltype(i)::value>(s, c); });
+}
+// The load part of a context: the page with entry e into ring stage `stage`.
+__device__ __forceinline__ void set_load(const VideoStream& s, uint32_t e, uint32_t stage, PageCtx& c) {
+  const uint64_t off = static_cast<uint64_t>(e >> 7) << 14;  // 16 KB tiles
+  c.ldk = reinterpret_cast<const uint16_t*>(reinterpret_cast<uint64_t>(s.kpool) + off);
+  c.ldv = reinterpret_cast<const uint16_t*>(reinterpret_cast<uint64_t>(s.vpool) + off);
+  c.lds = __builtin_amdgcn_readfirstlane(s.lds0 + stage);
+}
 
-// Waits for this wave's direct loads of the page after next's predecessor:
-// everything but the kDmaPerPage loads issued last (loads retire in order).
-// The barrier that follows then makes every wave's share visible.
+// Waits for this wave's direct loads of every page but the one issued last
+// (loads retire in order).  The barrier that follows then makes every wave's
+// share visible.
 __device__ __forceinline__ void wait_dma_all_but_last_page() {
-  static_assert(kDmaPerPage == 4, "vmcnt encoding below");
-  __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4), expcnt(7), lgkmcnt(15)
+  static_assert(kDmaPerPage == 8, "vmcnt encoding below");
+  __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8), expcnt(7), lgkmcnt(15)
 }
 __device__ __forceinline__ void wait_dma_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
-
-// max over lanes l and l ^ 32 (v_permlane32_swap: no LDS round trip)
-__device__ __forceinline__ float pair_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// The page barrier alone: no wait for the LDS reads in flight, which belong
+// to a page that stays.
+__device__ __forceinline__ void page_barrier() {
+  sched_fence();
+  asm volatile("s_barrier" ::: "memory");
+  sched_fence();
 }
 
-// v_max3 tree over one lane's 16 logits of a 32-key tile
-__device__ __forceinline__ float max16(const f32x16& s) {
-  const float a = fmaxf(s[0], fmaxf(s[1], s[2]));
-  const float b = fmaxf(s[3], fmaxf(s[4], s[5]));
-  const float c = fmaxf(s[6], fmaxf(s[7], s[8]));
-  const float d = fmaxf(s[9], fmaxf(s[10], s[11]));
-  const float e = fmaxf(s[12], fmaxf(s[13], s[14]));
-  return fmaxf(fmaxf(a, fmaxf(b, c)), fmaxf(d, fmaxf(e, s[15])));
-}
+template <class T>
+__device__ __forceinline__ void pin_s(T& x) { asm volatile("" : "+s"(x)); }
+template <class T>
+__device__ __forceinline__ void pin_v(T& x) { asm volatile("" : "+v"(x)); }
 
-// P = exp2(s) of a 32-key tile as bf16: pa holds the lane's first eight keys,
-// pb the next eight (the B operands of two P*V MFMAs).  Returns the lane's
-// row sum over the same bf16 values the MFMAs consume.
-__device__ __forceinline__ float exp_tile(const f32x16& s, u32x4& pa, u32x4& pb) {
-  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-  float la = 0.f, lb = 0.f;
+// The rest of a context: operand reads of the page in ring stage `stage`.
+__device__ __forceinline__ void set_reads(const VideoStream& s, uint32_t stage, PageCtx& c) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // bit-cast scalar temporaries: a bit-cast of a vector element subscript
-    // is lowered to element 0 by this compiler
-    const uint32_t x = pack_bf16(fast_exp2(s[2 * i]), fast_exp2(s[2 * i + 1]));
-    const uint32_t y = pack_bf16(fast_exp2(s[8 + 2 * i]), fast_exp2(s[9 + 2 * i]));
-    pa[i] = x;
-    pb[i] = y;
-    la = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), ones, la, false);
-    lb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, y), ones, lb, false);
+  for (int n = 0; n < 4; ++n) c.k[n] = (s.k_read + stage) ^ (64u * n);
+  c.v = s.v_read + stage;
+  c.vp = (s.v_read + ring_add(stage, kStages - 1)) ^ 64u;
+}
+
+// Starts the stream: key norms of its first window, the loads of its first
+// three pages, and the context of its first page.  (Past a stream's end the
+// last page is loaded once more, into a stage nothing reads.)
+__device__ __forceinline__ void stream_start(const AttnArgs& a, VideoStream& s) {
+  stream_combine(s);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) s.kn2[k] = a.knorm2[s.ent[k] >> 7];  // (past the end: the last unit's)
+  if (s.n == 0) return;
+  s.valid = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t e = stream_peek(s, min(k, s.n - 1));
+    s.valid |= (e & 127u) << (8 * k);
+    set_load(s, e, k * kStageBytes, s.c);
+    if (k < 3) issue_page(s, s.c);
   }
-  return la + lb;
+  set_reads(s, 0, s.c);
 }
 
-__device__ __forceinline__ void scale_o(VideoState& st, float alpha) {
-#pragma unroll
-  for (int t4 = 0; t4 < 4; ++t4) st.o[t4] *= alpha;
-}
-
-// Empty asm statements that make a value live in a register at this point:
-// they keep the compiler from sinking the speculative softmax past the rare
-// rescale branch, and a scalar page-list load from drifting next to its use.
-__device__ __forceinline__ void pin_sgpr(int x) { asm volatile("" ::"s"(x)); }
-__device__ __forceinline__ void pin_vgpr(u32x4& x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin_vgpr(float& x) { asm volatile("" : "+v"(x)); }
-
-template <int kStage>
-__device__ __forceinline__ uint16_t* stage_k() {
-  return kStage == 0 ? g_k0 : kStage == 1 ? g_k1 : kStage == 2 ? g_k2 : kStage == 3 ? g_k3 : g_k4;
-}
-template <int kStage>
-__device__ __forceinline__ uint16_t* stage_v() {
-  return kStage == 0 ? g_v0 : kStage == 1 ? g_v1 : kStage == 2 ? g_v2 : kStage == 3 ? g_v3 : g_v4;
-}
-__device__ __forceinline__ const uint16_t* stage_v_at(int stage) {
-  return stage == 0 ? g_v0 : stage == 1 ? g_v1 : stage == 2 ? g_v2 : stage == 3 ? g_v3 : g_v4;
-}
-
-// Page list index of the page staged three pages ahead of pi (near the
-// range's end the last page re-stages itself into an idle stage: nothing
-// reads that copy).
-__device__ __forceinline__ int ahead3(int pi, int p_end) { return pi + 3 < p_end ? pi + 3 : p_end - 1; }
-
-// A page for a wave whose 32 query rows are all padding (ragged last query
-// tile): it only issues its share of the loads of page pi + 3.
-template <int kCur>
-__device__ __forceinline__ void video_page_stage_only(const VideoCtx& c, int pi, int p_end) {
-  pi = __builtin_amdgcn_readfirstlane(pi);
-  const int ahead = c.pages[ahead3(pi, p_end)].x;
-  __syncthreads();
-  stage_dma(c, ahead, stage_k<(kCur + 3) % kStages>(), stage_v<(kCur + 3) % kStages>());
-  wait_dma_all_but_last_page();
-}
-
-// One 64-key page from LDS stage kCur, as two 32-key tiles (keys 0-31 in s0,
-// 32-63 in s1), scheduled by hand in 32 steps of one MFMA each:
-//   A: S tile 0                      B: S tile 1 + exp of tile 0
-//   D: P*V tile 0 + exp of tile 1    F: P*V tile 1
-// Each step issues the LDS operand read four steps ahead, its MFMA, and its
-// share of the softmax VALU work (two exponentials, one pack, one dot2), and
-// ends in a scheduling fence, so the emitted order is the program order.
-// The S accumulators start at -m_run (or -inf past the page's valid tokens),
-// so they hold the exp2 argument directly.
-//   kLazy = false: m_run is a fixed upper bound of the row's logits (from the
-//     key norms), so there is no running maximum and nothing to rescale.
-//   kLazy = true: m_run is a running maximum raised lazily.  The
-//     exponentials are taken speculatively against the current m_run; when a
-//     tile raises it by more than kLazyTau (rare after the first tile), a
-//     branch between the phases rescales O and l and recomputes that tile's P.
-// Right after the page's barrier, the direct loads of page pi + 3 into the
-// stage freed by page pi - 2 are issued; at the end of the page each wave
-// waits for its loads of page pi + 2 (issued one page earlier), so every
-// load has two pages to land and the next page is complete a page before it
-// is used.  One barrier per page.
-template <bool kLazy, int kCur>
-__device__ __forceinline__ void video_page(const VideoCtx& c, VideoState& st, int pi, int p_end) {
-  const uint16_t* sk = stage_k<kCur>();
-  const uint16_t* sv = stage_v<kCur>();
-  pi = __builtin_amdgcn_readfirstlane(pi);
-  const int n_valid = c.pages[pi].y;
-  const int ahead = c.pages[ahead3(pi, p_end)].x;
-  // both scalars are loaded before the barrier: a scalar load left for later
-  // would share lgkmcnt with the LDS operand reads
-  pin_sgpr(n_valid);
-  __syncthreads();
-  stage_dma(c, ahead, stage_k<(kCur + 3) % kStages>(), stage_v<(kCur + 3) % kStages>());
-  __builtin_amdgcn_sched_barrier(0);
-  const int half = c.half, l32 = c.l32;
-
-  const float neg_m = -st.m_run;
-  f32x16 s0, s1;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    s0[r] = neg_m;
-    s1[r] = neg_m;
-  }
-  // page tail: register r of half h holds key 16*(r/8) + 8*h + r%8 (+32 in
-  // s1); keys at or past n_valid become -inf
-  const bool tail = n_valid < kPageTokens;
-  auto mask_tail = [&](f32x16& sc, int key0) {
-    const int lim = n_valid - key0 - 8 * half;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (16 * (r >> 3) + (r & 7) >= lim) sc[r] = kNegInf;
-  };
-  // operand of S step n (n < 8: tile 0, else tile 1) and of P*V step n
-  // (d tile n % 4, key chunk n / 4)
-  auto kread = [&](int n) {
-    const int row = n < 8 ? l32 : 32 + l32;
-    return as_bf16x8(*reinterpret_cast<const u32x4*>(sk + row * kHeadDim + 8 * ((2 * (n & 7) + half) ^ (l32 & 15))));
-  };
-  auto vread = [&](int n) {
-    const int d = 32 * (n & 3) + l32;
-    return as_bf16x8(*reinterpret_cast<const u32x4*>(sv + d * kPageTokens + 8 * ((2 * (n >> 2) + half) ^ ((l32 >> 1) & 7))));
-  };
-  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-  // two exponentials of tile register pair n, packed to bf16 (word n of P),
-  // added to the row sum
-  auto exp_pair = [&](const f32x16& sc, int n, float& l) {
-    // bit-cast a scalar temporary: a bit-cast of a vector element subscript
-    // is lowered to element 0 by this compiler
-    const uint32_t w = pack_bf16(fast_exp2(sc[2 * n]), fast_exp2(sc[2 * n + 1]));
-    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, l, false);
-    return w;
-  };
-
-  // Operand reads run kAhead MFMA steps ahead of their use, through a ring of
-  // kAhead + 1 registers: S steps 0-15 (kread), then P*V steps 0-15 (vread).
-  constexpr int kAhead = 4;
-  auto oread = [&](int n) { return n < 16 ? kread(n) : vread(n - 16); };
-  bf16x8 ring[kAhead + 1];
-#pragma unroll
-  for (int n = 0; n < kAhead; ++n) ring[n] = oread(n);
-  auto next_operand = [&](int n) {  // operand of step n; issues the read of step n + kAhead
-    if (n + kAhead < 32) ring[(n + kAhead) % (kAhead + 1)] = oread(n + kAhead);
-    return ring[n % (kAhead + 1)];
-  };
-
-  // ---- A: S tile 0 ----
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const bf16x8 k = next_operand(n);
-    s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, c.qreg[n], s0, 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if (tail) mask_tail(s0, 0);
-  __builtin_amdgcn_sched_barrier(0);
-
-  // ---- B: S tile 1, exponentials of tile 0 ----
-  u32x4 p0a, p0b;
-  float l0 = 0.f, mx0 = 0.f;
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const bf16x8 k = next_operand(8 + n);
-    s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, c.qreg[n], s1, 0, 0, 0);
-    if (kLazy && n == 0) mx0 = pair_max(max16(s0));
-    const uint32_t w = exp_pair(s0, n, l0);
-    if (n < 4) p0a[n] = w; else p0b[n - 4] = w;
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // d0: shift of the running maximum taken at tile 0 (0 for most rows)
-  const bool need0 = kLazy && (st.first || mx0 > kLazyTau);
-  const float d0 = need0 ? mx0 : 0.f;
-  // keep the exponentials in the MFMA shadow they were scheduled in (the
-  // compiler would otherwise sink them past the branches below)
-  pin_vgpr(p0a);
-  pin_vgpr(p0b);
-  pin_vgpr(l0);
-  if constexpr (kLazy) {
-    if (__any(need0)) {
-      const float alpha = fast_exp2(-d0);
-      st.m_run += d0;
-      st.l_run *= alpha;
-      scale_o(st, alpha);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s0[r] -= d0;
-      l0 = exp_tile(s0, p0a, p0b);
-    }
-    st.first = false;
-  }
-  st.l_run += l0;
-  if (tail) mask_tail(s1, 32);
-  __builtin_amdgcn_sched_barrier(0);
-
-  // ---- D: P*V tile 0, exponentials of tile 1 ----
-  u32x4 p1a, p1b;
-  float l1 = 0.f, mx1 = 0.f;
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const bf16x8 v = next_operand(16 + n);
-    const int t4 = n & 3;
-    st.o[t4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, as_bf16x8(n < 4 ? p0a : p0b), st.o[t4], 0, 0, 0);
-    if (kLazy && n == 0) mx1 = pair_max(max16(s1));
-    const uint32_t w = exp_pair(s1, n, l1);
-    if (n < 4) p1a[n] = w; else p1b[n - 4] = w;
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // d1: shift of tile 1 relative to the page's starting maximum
-  const bool need1 = kLazy && mx1 - d0 > kLazyTau;
-  const float d1 = need1 ? mx1 : d0;
-  pin_vgpr(p1a);
-  pin_vgpr(p1b);
-  pin_vgpr(l1);
-  if constexpr (kLazy) {
-    if (__any(d1 != 0.f)) {
-      const float e = d1 - d0;
-      const float alpha = fast_exp2(-e);
-      st.m_run += e;
-      st.l_run *= alpha;
-      scale_o(st, alpha);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s1[r] -= d1;
-      l1 = exp_tile(s1, p1a, p1b);
-    }
-  }
-  st.l_run += l1;
-  __builtin_amdgcn_sched_barrier(0);
-
-  // ---- F: P*V tile 1 ----
-#pragma unroll
-  for (int n = 8; n < 16; ++n) {
-    const bf16x8 v = next_operand(16 + n);
-    const int t4 = n & 3;
-    st.o[t4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, as_bf16x8(n < 12 ? p1a : p1b), st.o[t4], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  wait_dma_all_but_last_page();
-}
-
-// Fixed-shift pages, software-pipelined across pages so that the softmax
-// VALU work is spread over the MFMA steps (it then runs in the shadow of the
-// matrix pipe instead of piling up in a few of them).  Iteration p (page p
-// from LDS stage kCur, V^T of page p-1 from the stage before it), 32 MFMA
-// steps with operand reads three steps ahead through a ring of four
-// registers; the last three steps read the first operands of page p + 1
-// (complete since the previous barrier), so the ring runs on across the page
-// barrier.  Exponentials per step in brackets ("register r" is accumulator
-// register r of a tile, in both lane halves; registers 0-7 are the tile's
-// first 16 keys):
-//   steps  0- 3  S tile 0 of p        [2: tile 1 of p-1, registers 0-3, 8-11]
-//   steps  4- 7  S tile 0 of p        [1: tile 1 of p-1, registers 4-7]
-//   steps  8-11  P*V of p-1, chunk 2  [1: tile 1 of p-1, registers 12-15]
-//   steps 12-15  P*V of p-1, chunk 3  [1: tile 0 of p, registers 0-3]
-//   steps 16-23  S tile 1 of p        [1: tile 0 of p, registers 4-11]
-//   steps 24-27  P*V of p, chunk 0    [1: tile 0 of p, registers 12-15]
-//   steps 28-31  P*V of p, chunk 1
-// Every P word is complete before the P*V step that reads it, and the
-// previous page's tile 1 is fully exponentiated (step 11) before this
-// page's tile 1 is accumulated (step 16), so their registers need not be
-// live together.  The first page of a range (kFirst) has no page p-1: steps
-// 0-7 S tile 0, 8-15 S tile 1 with the exponentials of tile 0 keys 0-15,
-// 16-23 P*V chunks 0-1 with those of keys 16-31.  Tile 1 of the last page is
-// finished by video_flush.
-constexpr int kRingAhead = 3;  // operand reads issued this many MFMA steps ahead
-struct PipeState {
-  f32x16 s1;      // S tile 1 of the previous page (exp2 argument)
-  bf16x8 ring[kRingAhead + 1];  // operands in flight (slot = step % 4)
+// A wave's query rows: kQT subtiles of 16.
+template <int kQT>
+struct VideoState {
+  f32x4 o[8][kQT];    // O^T[16 dt + 4 g + r][q]  (accumulation registers)
+  f32x4 l[kQT];       // row sums, the same in every register and lane group
+  f32x4 s_init[kQT];  // -m in every register: the S tiles start at the exp2 argument
+  float m[kQT];       // softmax shift of row q
+  bf16x8 q[kQT][4];   // Q''[q][32 s + 8 g .. + 8]
+  // across pages
+  f32x4 s3[kQT];      // S tile 3 of the previous page
+  u32x4 p1[kQT];      // P words of its chunk 1 (tile 2's done)
+  bf16x8 ring[4];     // operands in flight (slot = step % 4)
+  bool verify;        // some row's shift lies below its logit bound
+  bool in_reach;
+  u32x4 ones;         // bf16 ones (an opaque value: not rematerialised in front of an MFMA)
 };
+constexpr int kRingAhead = 3;  // operand reads issued this many steps ahead
 
-template <int kCur, bool kFirst>
-__device__ __forceinline__ void video_iter(const VideoCtx& c, VideoState& st, PipeState& ps,
-                                           const f32x16& s_init, int pi, int p_end) {
-  constexpr int kPrev = (kCur + kStages - 1) % kStages;
-  const uint16_t* sk = stage_k<kCur>();
-  const uint16_t* sv = stage_v<kCur>();
-  const uint16_t* svp = stage_v<kPrev>();
-  constexpr int kNext = (kCur + 1) % kStages;
-  const uint16_t* skn = stage_k<kNext>();
-  pi = __builtin_amdgcn_readfirstlane(pi);
-  const int ahead = c.pages[ahead3(pi, p_end)].x;
-  const int n_valid = c.pages[pi].y;
-  pin_sgpr(ahead);
-  pin_sgpr(n_valid);
-  __syncthreads();
-  stage_dma(c, ahead, stage_k<(kCur + 3) % kStages>(), stage_v<(kCur + 3) % kStages>());
-  __builtin_amdgcn_sched_barrier(0);
-  const int half = c.half, l32 = c.l32;
-  // Page tail (only a segment's last page is partly filled): logits of slots
-  // at or past n_valid become -inf before their exponentials, so they weigh
-  // exactly 0.  Register r of lane half h holds key 16 (r / 8) + 8 h + r % 8
-  // (+32 in tile 1).  A correction subtracted from the row sum afterwards
-  // would cancel catastrophically for rows whose logits all sit far below
-  // the shift.
+// The queries live in accumulation registers (an MFMA reads its operands from
+// either bank), which leaves the vector registers to the softmax.
+template <int kQT>
+__device__ __forceinline__ void pin_queries(VideoState<kQT>& st) {
+#pragma unroll
+  for (int j = 0; j < kQT; ++j)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) asm volatile("" : "+a"(st.q[j][t]));
+}
+
+// Two adjacent exponentials to one word of P.
+// The pins here and at the exponentials and S tiles keep them where they are
+// scheduled: the compiler would sink them past the branches of a page tail.
+__device__ __forceinline__ void put_word(u32x4& p, int word, float lo, float hi) {
+  uint32_t w = pack_bf16(lo, hi);
+  pin_v(w);
+  p[word] = w;
+}
+
+// One page, software-pipelined across pages so that the softmax work is
+// spread over the MFMA steps.  Iteration p (page p from the current stage,
+// V^T of page p - 1 from the one before it): 32 steps of one LDS operand read
+// (kRingAhead steps ahead, through a ring of four registers that runs on
+// across the page barrier) and kQT MFMAs, one per subtile:
+//   steps  0- 7  S tiles 0 and 1 of p       exponentials of tile 3 of p - 1
+//   steps  8-15  P*V of p - 1, chunk 1      tile 0 of p (from step 10)
+//   steps 16-23  S tiles 2 and 3 of p       tile 1 of p
+//   steps 24-31  P*V of p, chunk 0          tile 2 of p (from step 26)
+// The subtiles' exponentials run in kQT / 2 streams, one exponential per
+// stream and step (two in steps 10, 11, 26 and 27), each issued behind an MFMA
+// of its own (an exponential takes 8 of the 16 cycles of an MFMA, a pack 4)
+// and packed behind the next one, and each slot ends in a scheduling fence,
+// so that the emitted order is the program order.  Every P word is complete
+// before the P*V step that reads it.  Steps 0-7 also issue the direct loads
+// of page p + 3 into the stage freed by page p - 2; at the end of the page
+// each wave waits for its loads of page p + 2, so every load has two pages to
+// land and the next page is complete a page before it is used.  One barrier
+// per page.
+// kFirst: a range's first page: no page p - 1; with st.verify set it also
+// checks that the shift is in reach of the rows' logits (st.in_reach).
+template <int kQT, bool kFirst>
+__device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) {
+  const int n_valid = static_cast<int>(s.valid & 0xffu);
   const bool tail = n_valid < kPageTokens;
-  auto mask_tail = [&](f32x16& sc, int key0) {
-    const int lim = n_valid - key0 - 8 * half;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (16 * (r >> 3) + (r & 7) >= lim) sc[r] = kNegInf;
+  const PageCtx c = s.c;
+  PageCtx nx;
+  pin_queries(st);
+  pin_v(st.ones);
+  page_barrier();
+  // operand of step n
+  auto oread = [&](auto nc) __attribute__((always_inline)) {
+    constexpr int n = decltype(nc)::value;
+    if constexpr (n >= 32) return lds_read16(nx.k[n - 32]);
+    else if constexpr (n < 8) return lds_read16(c.k[n & 3] + 4096u * (n >> 2));
+    else if constexpr (n < 16) return lds_read16(c.vp + 2048u * (n - 8));
+    else if constexpr (n < 24) return lds_read16(c.k[n & 3] + 4096u * (2 + ((n - 16) >> 2)));
+    else return lds_read16(c.v + 2048u * (n - 24));
   };
-  auto kread_at = [&](const uint16_t* k, int n) {  // S k-step n % 8 of tile n / 8
-    const int row = n < 8 ? l32 : 32 + l32;
-    return as_bf16x8(*reinterpret_cast<const u32x4*>(k + row * kHeadDim + 8 * ((2 * (n & 7) + half) ^ (l32 & 15))));
-  };
-  auto kread = [&](int n) { return kread_at(sk, n); };
-  auto vread = [&](const uint16_t* v, int t4, int jc) {  // d tile t4, key chunk jc
-    const int d = 32 * t4 + l32;
-    return as_bf16x8(*reinterpret_cast<const u32x4*>(v + d * kPageTokens + 8 * ((2 * jc + half) ^ ((l32 >> 1) & 7))));
-  };
-  constexpr int kSteps = kFirst ? 24 : 32;
-  static_assert(kSteps % (kRingAhead + 1) == 0, "ring slots must line up across iterations");
-  auto oread = [&](int o) {
-    if (o >= kSteps) return kread_at(skn, o - kSteps);  // page p + 1, first S steps
-    if (kFirst) return o < 16 ? kread(o) : vread(sv, (o - 16) & 3, (o - 16) >> 2);
-    if (o < 8) return kread(o);
-    if (o < 12) return vread(svp, o - 8, 2);
-    if (o < 16) return vread(svp, o - 12, 3);
-    if (o < 24) return kread(8 + o - 16);
-    return vread(sv, (o - 24) & 3, (o - 24) >> 2);
-  };
-  constexpr int kAhead = kRingAhead;
-  bf16x8* ring = ps.ring;
-  if (kFirst) {  // the range's first page: nothing was read ahead
-#pragma unroll
-    for (int o = 0; o < kAhead; ++o) ring[o] = oread(o);
+  if constexpr (kFirst) {
+    static_for<kRingAhead>([&](auto n) __attribute__((always_inline)) { st.ring[decltype(n)::value] = oread(n); });
   }
-  __builtin_amdgcn_sched_barrier(0);
+  f32x4 sa[4][kQT];
+  u32x4 p0[kQT], p1n[kQT];
+  float e[kQT / 2][32];  // exponential x of a stream: tile x / 8, subtile (x / 4) % 2, register x % 4
 
-  // The first MFMA of each S tile takes its accumulator input from s_init
-  // (-m_run in every register), so the tiles start at the exp2 argument with
-  // no per-page register initialisation.
-  f32x16 s0, s1;
-  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-  float l = 0.f;
-  // P words: w[0..3] keys 0-15 of a tile (chunk 0 or 2), w[4..7] keys 16-31
-  u32x4 pp2, pp3, p0, p1;  // tile 1 of p-1 (chunks 2, 3); tile 0 of p (chunks 0, 1)
-  float e_lo = 0.f;        // first exponential of a pair, waiting for its partner
-  float e2_lo = 0.f, e3_lo = 0.f;  // the same for the two halves of the previous tile 1
-  auto exp_one = [&](const f32x16& sc, int r, u32x4& dst, int word) {
-    const float e = fast_exp2(sc[r]);
-    if ((r & 1) == 0) {
-      e_lo = e;
+  auto exp_x = [&](auto kc_, auto xc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc_)::value, x = decltype(xc)::value;
+    constexpr int t = x >> 3, j = 2 * k + ((x >> 2) & 1), r = x & 3;
+    if constexpr (t == 3) {
+      if constexpr (!kFirst) { e[k][x] = fast_exp2(st.s3[j][r]); pin_v(e[k][x]); }
     } else {
-      // bit-cast a scalar temporary: a bit-cast of a vector element subscript
-      // is lowered to element 0 by this compiler
-      const uint32_t w = pack_bf16(e_lo, e);
-      l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, l, false);
-      dst[word] = w;
+      e[k][x] = fast_exp2(sa[t][j][r]);
+      pin_v(e[k][x]);
     }
   };
-
-#pragma unroll
-  for (int o = 0; o < kSteps; ++o) {
-    const bf16x8 a = ring[o % (kAhead + 1)];
-    ring[(o + kAhead) % (kAhead + 1)] = oread(o + kAhead);
-    if (kFirst) {
-      if (o < 8) {
-        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c.qreg[o], o == 0 ? s_init : s0, 0, 0, 0);
-      } else if (o < 16) {
-        s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c.qreg[o - 8], o == 8 ? s_init : s1, 0, 0, 0);
-        if (o == 8 && tail) mask_tail(s0, 0);
-        exp_one(s0, o - 8, p0, (o - 8) >> 1);
-      } else if (o < 20) {
-        st.o[o - 16] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(p0), st.o[o - 16], 0, 0, 0);
-        exp_one(s0, 8 + 2 * (o - 16), p1, o - 16);
-        exp_one(s0, 9 + 2 * (o - 16), p1, o - 16);
-      } else {
-        st.o[o - 20] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(p1), st.o[o - 20], 0, 0, 0);
-      }
+  auto pack_x = [&](auto kc_, auto xc) __attribute__((always_inline)) {  // words of exponentials x, x + 1 (x even)
+    constexpr int k = decltype(kc_)::value, x = decltype(xc)::value;
+    constexpr int t = x >> 3, j = 2 * k + ((x >> 2) & 1), word = 2 * (t & 1) + ((x & 3) >> 1);
+    if constexpr (t == 3) {
+      if constexpr (!kFirst) put_word(st.p1[j], word, e[k][x], e[k][x + 1]);
+    } else if constexpr (t == 2) {
+      put_word(p1n[j], word, e[k][x], e[k][x + 1]);
     } else {
-      // exponentials of the previous page's tile 1: registers 0-7 (key chunk
-      // 2) one per step in steps 0-7, registers 8-11 a second one in steps
-      // 0-3 and 12-15 one per step in 8-11, all done before the P*V of
-      // chunks 2 and 3 reads them; those of this page's tile 0 one per step
-      // in steps 12-27 (registers 0-7 before chunk 0 is read at step 24)
-      auto prev_exp = [&](int r, u32x4& dst) {
-        const float e = fast_exp2(ps.s1[r]);
-        if ((r & 1) == 0) {
-          if (r < 8) e2_lo = e; else e3_lo = e;
-        } else {
-          const uint32_t w = pack_bf16(r < 8 ? e2_lo : e3_lo, e);
-          l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, l, false);
-          dst[(r & 7) >> 1] = w;
+      put_word(p0[j], word, e[k][x], e[k][x + 1]);
+    }
+  };
+  // a page tail's work on the chunk of tiles a and a + 1
+  auto check_chunk = [&](auto ac) __attribute__((always_inline)) {
+    constexpr int a = decltype(ac)::value;
+    if (tail) {
+      // logits of slots at or past n_valid become -inf, so they weigh exactly
+      // 0 (a correction subtracted from the row sum afterwards would cancel
+      // for rows whose logits all sit far below the shift)
+      const int lim = n_valid - 8 * (opaque(s.lane) >> 4);
+#pragma unroll
+      for (int t = a; t < a + 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < kQT; ++j)
+            sa[t][j][r] = 32 * (t >> 1) + 4 * (t & 1) + r >= lim ? kNegInf : sa[t][j][r];
+    }
+    if constexpr (kFirst && a == 0) {
+      if (st.verify) {  // the S tiles hold logit - m
+        bool in_reach = true;
+#pragma unroll
+        for (int j = 0; j < kQT; ++j) {
+          const float mx = fmaxf(fmaxf(fmaxf(sa[0][j][0], sa[0][j][1]), fmaxf(sa[0][j][2], sa[0][j][3])),
+                                 fmaxf(fmaxf(sa[1][j][0], sa[1][j][1]), fmaxf(sa[1][j][2], sa[1][j][3])));
+          // (rows with the bound itself as their shift are in reach anyway)
+          in_reach = in_reach && pair_max<32>(pair_max<16>(mx)) >= -kShiftReach;
         }
-      };
-      if (o < 8) {
-        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c.qreg[o], o == 0 ? s_init : s0, 0, 0, 0);
-        prev_exp(o, pp2);
-        if (o < 4) prev_exp(8 + o, pp3);
-      } else if (o < 12) {
-        st.o[o - 8] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pp2), st.o[o - 8], 0, 0, 0);
-        prev_exp(12 + o - 8, pp3);
-      } else if (o < 16) {
-        st.o[o - 12] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pp3), st.o[o - 12], 0, 0, 0);
-        if (o == 12 && tail) mask_tail(s0, 0);
-        exp_one(s0, o - 12, p0, (o - 12) >> 1);
-      } else if (o < 24) {
-        s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c.qreg[o - 16], o == 16 ? s_init : s1, 0, 0, 0);
-        const int r = 4 + o - 16;
-        exp_one(s0, r, r < 8 ? p0 : p1, (r & 7) >> 1);
-      } else if (o < 28) {
-        st.o[o - 24] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(p0), st.o[o - 24], 0, 0, 0);
-        const int r = 12 + o - 24;
-        exp_one(s0, r, p1, (r & 7) >> 1);
-      } else {
-        st.o[o - 28] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(p1), st.o[o - 28], 0, 0, 0);
+        st.in_reach = __all(in_reach);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  st.l_run += l;
-  if (tail) mask_tail(s1, 32);
-  ps.s1 = s1;
-  wait_dma_all_but_last_page();
-}
+    sched_fence();
+  };
 
-// Finishes tile 1 of the range's last page (V^T in LDS stage `stage`).
-__device__ __forceinline__ void video_flush(const VideoCtx& c, VideoState& st, const PipeState& ps,
-                                            int stage) {
-  const uint16_t* sv = stage_v_at(stage);
-  const int half = c.half, l32 = c.l32;
-  u32x4 pa, pb;
-  st.l_run += exp_tile(ps.s1, pa, pb);
+  // the next page's context, one small piece per step
+  int look = 0;
+  uint32_t ent = 0, st_next = 0;
+  auto next_ctx = [&](auto oc) __attribute__((always_inline)) {
+    constexpr int o = decltype(oc)::value;
+    if constexpr (o == 12) { look = min(s.at + 4, s.n - 1); pin_s(look); }
+    if constexpr (o == 13) { ent = __builtin_amdgcn_readlane(s.ent[0], look & 63); pin_s(ent); }
+    if constexpr (o == 14) {
+      const uint32_t e1 = __builtin_amdgcn_readlane(s.ent[1], look & 63);
+      ent = (look & 64) ? e1 : ent;
+      pin_s(ent);
+    }
+    if constexpr (o == 15) { st_next = ring_add(s.stage, 1); pin_s(st_next); }
+    if constexpr (o == 16) {
+      nx.ldk = reinterpret_cast<const uint16_t*>(reinterpret_cast<uint64_t>(s.kpool) + (static_cast<uint64_t>(ent >> 7) << 14));
+      pin_s(nx.ldk);
+    }
+    if constexpr (o == 17) {
+      nx.ldv = reinterpret_cast<const uint16_t*>(reinterpret_cast<uint64_t>(s.vpool) + (static_cast<uint64_t>(ent >> 7) << 14));
+      pin_s(nx.ldv);
+    }
+    if constexpr (o == 18) { nx.lds = s.lds0 + ring_add(st_next, 3); pin_s(nx.lds); }
+    if constexpr (o == 19) { nx.k[0] = s.k_read + st_next; pin_v(nx.k[0]); }
+    if constexpr (o == 20) { nx.k[1] = nx.k[0] ^ 64u; pin_v(nx.k[1]); }
+    if constexpr (o == 21) { nx.k[2] = nx.k[0] ^ 128u; pin_v(nx.k[2]); }
+    if constexpr (o == 22) { nx.k[3] = nx.k[0] ^ 192u; pin_v(nx.k[3]); }
+    if constexpr (o == 23) { nx.v = s.v_read + st_next; pin_v(nx.v); }
+    if constexpr (o == 24) { nx.vp = c.v ^ 64u; pin_v(nx.vp); }
+    if constexpr (o == 28) { s.valid = __builtin_amdgcn_readfirstlane((s.valid >> 8) | ((ent & 127u) << 24)); }
+  };
+  static_for<32>([&](auto oc) __attribute__((always_inline)) {
+    constexpr int o = decltype(oc)::value;
+    const bf16x8 a = st.ring[o & 3];
+    static_for<kQT>([&](auto jc) __attribute__((always_inline)) {
+      constexpr int j = decltype(jc)::value, k = j >> 1;
+      constexpr bool even = (j & 1) == 0;
+      // ---- the MFMA ----
+      if constexpr (o < 8 || (o >= 16 && o < 24)) {
+        constexpr int t = (o < 8 ? 0 : 2) + ((o & 7) >> 2);
+        if constexpr ((o & 3) == 0) mfma_s(sa[t][j], a, st.q[j][0], st.s_init[j]);
+        else mfma_s(sa[t][j], a, st.q[j][o & 3], sa[t][j]);
+        pin_v(sa[t][j]);
+      } else if constexpr (o < 16) {
+        if constexpr (!kFirst) {
+          mfma_o(st.o[o - 8][j], a, as_bf16x8(st.p1[j]));
+          if constexpr (o == 15) mfma_o(st.l[j], as_bf16x8(st.ones), as_bf16x8(st.p1[j]));
+        }
+      } else {
+        if constexpr (kFirst) mfma_o_first(st.o[o - 24][j], a, as_bf16x8(p0[j]));
+        else mfma_o(st.o[o - 24][j], a, as_bf16x8(p0[j]));
+        if constexpr (o == 31) {
+          if constexpr (kFirst) mfma_o_first(st.l[j], as_bf16x8(st.ones), as_bf16x8(p0[j]));
+          else mfma_o(st.l[j], as_bf16x8(st.ones), as_bf16x8(p0[j]));
+        }
+      }
+      sched_fence();
+      // ---- this slot's share of the rest ----
+      if constexpr (j == 1) {
+        constexpr int n = o + kRingAhead;
+        if constexpr (!(kFirst && n >= 8 && n < 16)) st.ring[n & 3] = oread(Const<n>{});
+      }
+      if constexpr (even) {
+        if constexpr (o < 8) exp_x(Const<k>{}, Const<24 + o>{});
+        else if constexpr (o == 10) exp_x(Const<k>{}, Const<0>{});
+        else if constexpr (o == 11) exp_x(Const<k>{}, Const<2>{});
+        else if constexpr (o >= 12 && o < 24) exp_x(Const<k>{}, Const<o - 8>{});
+        else if constexpr (o == 26) exp_x(Const<k>{}, Const<16>{});
+        else if constexpr (o == 27) exp_x(Const<k>{}, Const<18>{});
+        else if constexpr (o >= 28) exp_x(Const<k>{}, Const<o - 8>{});
+      } else {
+        if constexpr (o < 8 && (o & 1)) pack_x(Const<k>{}, Const<24 + o - 1>{});
+        else if constexpr (o == 10) exp_x(Const<k>{}, Const<1>{});
+        else if constexpr (o == 11) { exp_x(Const<k>{}, Const<3>{}); pack_x(Const<k>{}, Const<0>{}); }
+        else if constexpr (o == 12) pack_x(Const<k>{}, Const<2>{});
+        else if constexpr (o > 12 && o < 24 && (o & 1)) pack_x(Const<k>{}, Const<o - 9>{});
+        else if constexpr (o == 26) exp_x(Const<k>{}, Const<17>{});
+        else if constexpr (o == 27) { exp_x(Const<k>{}, Const<19>{}); pack_x(Const<k>{}, Const<16>{}); }
+        else if constexpr (o == 28) pack_x(Const<k>{}, Const<18>{});
+        else if constexpr (o > 28 && (o & 1)) pack_x(Const<k>{}, Const<o - 9>{});
+        if constexpr (k == kQT / 2 - 1 && o < kDmaPerPage) issue_load<o>(s, c);
+        if constexpr (k == kQT / 2 - 1) next_ctx(oc);
+        if constexpr (k == kQT / 2 - 1 && (o == 14 || o == 30)) pin_v(st.ones);
+      }
+      sched_fence();
+    });
+    if constexpr (o == 9) check_chunk(Const<0>{});
+    if constexpr (o == 25) check_chunk(Const<2>{});
+  });
 #pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    const int t4 = n & 3, jc = 2 + (n >> 2);
-    const int d = 32 * t4 + l32;
-    const bf16x8 v =
-        as_bf16x8(*reinterpret_cast<const u32x4*>(sv + d * kPageTokens + 8 * ((2 * jc + half) ^ ((l32 >> 1) & 7))));
-    st.o[t4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, as_bf16x8(n < 4 ? pa : pb), st.o[t4], 0, 0, 0);
+  for (int j = 0; j < kQT; ++j) {
+    st.s3[j] = sa[3][j];
+    st.p1[j] = p1n[j];
   }
+  // After a range's first page everything is waited for: a load the compiler
+  // knows of and believes in flight on entry to the page loop would be waited
+  // for in every iteration, with all the direct loads behind it.
+  if constexpr (kFirst) wait_dma_all();
+  else wait_dma_all_but_last_page();
+  s.c = nx;
+  s.at += 1;
+  s.stage = st_next;
+  stream_reach(s);
 }
 
-// One segment of a video workgroup's work: the query tile of rows
-// [q_lo, min(q_lo + 256, q_hi)) of head `head` against entries
-// [p_begin, p_end) of the call's page list, which is key range `seg` of the
-// n_seg ranges that split this head's pages (q_hi ends the tile's query
-// class).  With one range the output is written in bf16; otherwise the
-// softmax-normalised partial and its log-sum-exp go to the split-KV
-// workspace for the combine kernel.
+// Finishes the last page of a range (its stage is the one before the
+// stream's current): tile 3's exponentials, then the P*V of chunk 1.
+template <int kQT>
+__device__ __forceinline__ void video_flush(VideoState<kQT>& st, const VideoStream& s) {
+  const uint32_t v1 = s.c.vp;
+  mfma_drain();
+#pragma unroll
+  for (int j = 0; j < kQT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; r += 2)
+      put_word(st.p1[j], 2 + (r >> 1), fast_exp2(st.s3[j][r]), fast_exp2(st.s3[j][r + 1]));
+  bf16x8 v[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) v[dt] = lds_read16(v1 + 2048u * dt);
+  pin_v(st.ones);
+  mfma_drain();
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) mfma_o(st.l[j], as_bf16x8(st.ones), as_bf16x8(st.p1[j]));
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+    for (int j = 0; j < kQT; ++j) mfma_o(st.o[dt][j], v[dt], as_bf16x8(st.p1[j]));
+  mfma_drain();
+}
+
+// Advances the stream by a page, context and all (the pipelined iteration does
+// the same a little at a time).
+__device__ __forceinline__ void stream_advance(VideoStream& s) {
+  const uint32_t e = stream_peek(s, min(s.at + 4, s.n - 1));
+  s.valid = (s.valid >> 8) | ((e & 127u) << 24);
+  s.at += 1;
+  s.stage = ring_add(s.stage, 1);
+  set_load(s, e, ring_add(s.stage, 3), s.c);
+  set_reads(s, s.stage, s.c);
+  stream_reach(s);
+}
+
+// One page under a running maximum, subtile by subtile, not pipelined: for
+// rows whose shift cannot be fixed in advance (logits more than kShiftReach
+// below a bound above kShiftBoundMax, or the option that asks for it).
+// Starts from m = -inf with O and l zero.
+template <int kQT>
+__device__ __forceinline__ void video_page_running_max(VideoState<kQT>& st, const VideoStream& s, uint32_t stage,
+                                                       int n_valid) {
+  const uint32_t k0 = s.k_read + stage, v0 = s.v_read + stage;
+  const int lim = n_valid - 8 * (opaque(s.lane) >> 4);
+  static_for<kQT>([&](auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    f32x4 sa[4];
+    float mx = kNegInf;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      sa[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int n = 0; n < 4; ++n) mfma_s(sa[t], lds_read16((k0 ^ (64u * n)) + 4096u * t), st.q[j][n], sa[t]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        sa[t][r] = 32 * (t >> 1) + 4 * (t & 1) + r >= lim ? kNegInf : sa[t][r];
+        mx = fmaxf(mx, sa[t][r]);
+      }
+    }
+    mx = pair_max<32>(pair_max<16>(mx));  // a page has a valid key: not -inf
+    const float m = fmaxf(st.m[j], mx);
+    if (__any(m != st.m[j])) {
+      const float alpha = fast_exp2(st.m[j] - m);
+      mfma_drain();
+      st.l[j] *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) st.o[dt][j] *= alpha;
+    }
+    st.m[j] = m;
+    u32x4 p[2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; r += 2)
+        p[t >> 1][2 * (t & 1) + (r >> 1)] = pack_bf16(fast_exp2(sa[t][r] - m), fast_exp2(sa[t][r + 1] - m));
+    pin_v(p[0]);
+    pin_v(p[1]);
+    pin_v(st.ones);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      bf16x8 v[8];
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) v[dt] = lds_read16((v0 ^ (64u * c)) + 2048u * dt);
+      mfma_drain();
+      mfma_o(st.l[j], as_bf16x8(st.ones), as_bf16x8(p[c]));
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) mfma_o(st.o[dt][j], v[dt], as_bf16x8(p[c]));
+    }
+    mfma_drain();
+  });
+}
+
+// One segment of a video workgroup's stream: the query tile of rows
+// [q_lo, min(q_lo + 256, q_hi)) of head `head` against n pages of the stream,
+// which are key range `seg` of the ranges that split this head's pages
+// (`whole`: the only one; q_hi ends the tile's query class).  With one range
+// the output is written in bf16; otherwise the softmax-normalised partial and
+// its log-sum-exp go to the split-KV workspace for the combine kernel.
 struct VideoSeg {
-  int head, p_begin, p_end, seg, n_seg, q_lo, q_hi;
+  int head, n, seg, q_lo, q_hi;
+  bool whole;
 };
 
-__device__ __forceinline__ void video_segment(const AttnArgs& a, const VideoSeg& sg, bool first_segment) {
-  // Lane-derived values (LDS and load offsets) are recomputed per segment:
-  // kept live across the segment loop they would push the page loop into
-  // register spills.
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int half = lane >> 5, l32 = lane & 31;
-  const int head = sg.head, p_begin = sg.p_begin, p_end = sg.p_end;
-
-  VideoCtx c;
-  c.pages = page_list(a);
-  c.page_stride = static_cast<int64_t>(a.num_heads) * kPageHeadElems;
-  c.kpool = a.kpool + head * kPageHeadElems;
-  c.vpool = a.vpool + head * kPageHeadElems;
-  // The wave's rows: video rows of q, and at and past rq_row0 (the end of
-  // the video rows) rider rows, the prepared rows of rq that see the same
-  // pages; a wave may hold both.
-  const int wrow = sg.q_lo + wave * 32;
-  c.active = wrow < sg.q_hi || (a.n_rq > 0 && wrow < a.rq_row0 + a.n_rq && wrow + 32 > a.rq_row0);
-  c.wave = wave;
-  c.half = half;
-  c.l32 = l32;
-  {
-    const int r0 = 4 * wave + (lane >> 4);  // K row of block i = 0
-    c.dma_k = 2 * k_tile_index(swap23(r0), 8 * ((lane & 15) ^ (r0 & 15)));
-    const int d0 = 8 * wave + (lane >> 3);  // V^T row of block i = 0
-    c.dma_v = 2 * v_tile_index(8 * ((lane & 7) ^ ((d0 >> 1) & 7)), d0);
+// A wave's query rows as the call gives them: raw[j][s] = Q[row j][32 s + 8 g .. + 8].
+template <int kQT>
+struct RawQueries {
+  u32x4 raw[kQT][4];
+  bool rider[kQT];  // rider rows (at and past rq_row0): prepared rows of their own
+  bool ok[kQT];
+  int3 pos[kQT];
+};
+template <int kQT, bool kPrepared>
+__device__ __forceinline__ void fetch_queries(const AttnArgs& a, const VideoSeg& sg, int wrow, int lane,
+                                              RawQueries<kQT>& x) {
+  const int lane_o = opaque(lane), g = lane_o >> 4, i16 = lane_o & 15;
+  // row j's pointer is the first row's plus 16 j token strides (uniform);
+  // rows past the end read the zero block (zeros cost the matrix pipe little)
+  const uint16_t* qp = a.q + sg.head * a.q_head_stride + (wrow + i16) * a.q_tok_stride + 8 * g;
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) {
+    const int row = wrow + 16 * j + i16;
+    x.ok[j] = row < sg.q_hi;
+    x.rider[j] = false;
+    const uint16_t* p = x.ok[j] ? qp + 16 * j * a.q_tok_stride : a.zeros + 8 * g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x.raw[j][s] = *reinterpret_cast<const u32x4*>(p + 32 * s);
+    x.pos[j] = make_int3(0, 0, 0);
+    if (!kPrepared && a.mode == 1 && x.ok[j])
+      x.pos[j] = make_int3(a.positions[3 * row], a.positions[3 * row + 1], a.positions[3 * row + 2]);
   }
-
-  // Prologue loads, issued so that no dependent load waits behind an
-  // unrelated one (vector memory counters complete in order): the page-list
-  // entries of the first three pages are scalar loads; then every
-  // independent vector load (positions, the page-list entries of the
-  // key-norm scan, Q, gamma); then the direct loads of the first three pages
-  // (a later segment first waits for every wave to be done with the
-  // previous segment's stages); then the loads that depend on the first
-  // batch (key norms, rotary table entries).
-  int pg_first[3] = {0, 0, 0};
-  if (p_begin < p_end) {
+  if (a.n_rq > 0 && wrow + 16 * kQT > a.rq_row0) {  // rider rows among them
 #pragma unroll
-    for (int k = 0; k < 3; ++k) pg_first[k] = c.pages[min(p_begin + k, p_end - 1)].x;
-  }
-  const bool rider = a.n_rq > 0 && wrow + l32 >= a.rq_row0;  // the same in both halves of a row
-  const int q = wrow + l32 - (rider ? a.rq_row0 : 0);
-  const bool q_ok = q < (rider ? a.n_rq : sg.q_hi);
-  const bool norm_rope = !rider && a.mode == 1;
-  int3 qpos = make_int3(0, 0, 0);
-  if (norm_rope && q_ok) qpos = make_int3(a.positions[3 * q], a.positions[3 * q + 1], a.positions[3 * q + 2]);
-  // the segment's page-list entries (two per lane in the first pass)
-  int pgl[2];
+    for (int j = 0; j < kQT; ++j) {
+      const int q = wrow + 16 * j + i16 - a.rq_row0;
+      if (q >= 0 && q < a.n_rq) {
+        const uint16_t* p = a.rq + q * a.rq_tok_stride + sg.head * a.rq_head_stride + 8 * g;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int pi = p_begin + lane + 64 * k;
-    pgl[k] = pi < p_end ? c.pages[pi].x : -1;
-  }
-  u32x4 qraw[8];
-  const uint16_t* qp = rider ? a.rq + q * a.rq_tok_stride + head * a.rq_head_stride + 8 * half
-                             : a.q + q * a.q_tok_stride + head * a.q_head_stride + 8 * half;
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-    qraw[s] = q_ok ? *reinterpret_cast<const u32x4*>(qp + 16 * s) : (u32x4){0u, 0u, 0u, 0u};
-  float gam[8][8];
-  if (norm_rope) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const float4 g0 = *reinterpret_cast<const float4*>(a.gamma + 16 * s + 8 * half);
-      const float4 g1 = *reinterpret_cast<const float4*>(a.gamma + 16 * s + 8 * half + 4);
-      gam[s][0] = g0.x; gam[s][1] = g0.y; gam[s][2] = g0.z; gam[s][3] = g0.w;
-      gam[s][4] = g1.x; gam[s][5] = g1.y; gam[s][6] = g1.z; gam[s][7] = g1.w;
+        for (int s = 0; s < 4; ++s) x.raw[j][s] = *reinterpret_cast<const u32x4*>(p + 32 * s);
+        x.rider[j] = true;
+      }
     }
   }
-  if (!first_segment) __syncthreads();
-  if (p_begin < p_end) {
-    stage_dma(c, pg_first[0], g_k0, g_v0);
-    stage_dma(c, pg_first[1], g_k1, g_v1);
-    stage_dma(c, pg_first[2], g_k2, g_v2);
-  }
-  // key norms of the segment's pages
-  float kn2 = 0.f;
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    if (pgl[k] >= 0) kn2 = fmaxf(kn2, a.knorm2[static_cast<int64_t>(pgl[k]) * a.num_heads + head]);
-  for (int pi = p_begin + lane + 128; pi < p_end; pi += 64)  // segments longer than 128 pages
-    kn2 = fmaxf(kn2, a.knorm2[static_cast<int64_t>(c.pages[pi].x) * a.num_heads + head]);
+}
 
-  // ---- Q prologue: lane holds Q''[q][16s + 8h + j], s = 0..7, j = 0..7 ----
-  if (norm_rope) {
+// The prepared queries, st.q[j][s] = Q''[row j][32 s + 8 g .. + 8], by the
+// call's query mode (kPrepared: 2, given as they are, else 0 or 1); rider rows
+// (at and past rq_row0) come prepared.
+template <int kQT, bool kPrepared>
+__device__ __forceinline__ void prepare_rows(const AttnArgs& a, const RawQueries<kQT>& x, int g, VideoState<kQT>& st) {
+  if (kPrepared) {
+#pragma unroll
+    for (int j = 0; j < kQT; ++j)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) st.q[j][s] = as_bf16x8(x.raw[j][s]);
+    return;
+  }
+  if (a.mode == 0) {
+#pragma unroll
+    for (int j = 0; j < kQT; ++j) {
+      const float sc = x.rider[j] ? 1.0f : a.scale_log2;  // riders: x 1 is exact
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = pack_bf16(bf16_lo(x.raw[j][s][i]) * sc, bf16_hi(x.raw[j][s][i]) * sc);
+        st.q[j][s] = as_bf16x8(w);
+      }
+    }
+    return;
+  }
+  // Norm and rotation.  The lane's 16 pairs are 16 s + 4 g + i; a pair's band
+  // is a select on its index (no branch), the table rows' offsets are per row.
+  const int p0 = a.rope.pairs[0], p01 = p0 + a.rope.pairs[1];
+  float inv[kQT];
+  const float2* row[kQT][3];
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) {
     int pt = 0, ph = 0, pw = 0;
-    if (q_ok) clamp_pos(a.rope, qpos.x, qpos.y, qpos.z, a.flags, pt, ph, pw);
+    if (x.ok[j] && !x.rider[j]) clamp_pos(a.rope, x.pos[j].x, x.pos[j].y, x.pos[j].z, a.flags, pt, ph, pw);
+    row[j][0] = a.rope.tab[0] + static_cast<int64_t>(pt) * a.rope.pairs[0];
+    row[j][1] = a.rope.tab[1] + static_cast<int64_t>(ph) * a.rope.pairs[1] - p0;
+    row[j][2] = a.rope.tab[2] + static_cast<int64_t>(pw) * a.rope.pairs[2] - p01;
     float ss = 0.f;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int s = 0; s < 4; ++s) ss = norm2_words(x.raw[j][s], ss);
+    ss = pair_sum<32>(pair_sum<16>(ss));
+    inv[j] = rsqrtf(ss * (1.0f / kHeadDim) + a.eps);
+  }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float x0 = bf16_lo(qraw[s][i]), x1 = bf16_hi(qraw[s][i]);
-        ss += x0 * x0 + x1 * x1;
-      }
-    ss += __shfl_xor(ss, 32);
-    const float inv = rsqrtf(ss * (1.0f / kHeadDim) + a.eps);
+  for (int s = 0; s < 4; ++s) {
+    const float4 g0 = *reinterpret_cast<const float4*>(a.gamma + 32 * s + 8 * g);
+    const float4 g1 = *reinterpret_cast<const float4*>(a.gamma + 32 * s + 8 * g + 4);
+    const float gam[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+    float2 cs[kQT][4];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int d0 = 16 * s + 8 * half;
+    for (int i = 0; i < 4; ++i) {
+      const int p = 16 * s + 4 * g + i;
+#pragma unroll
+      for (int j = 0; j < kQT; ++j) cs[j][i] = (p < p0 ? row[j][0] : p < p01 ? row[j][1] : row[j][2])[p];
+    }
+#pragma unroll
+    for (int j = 0; j < kQT; ++j) {
       u32x4 w;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float y0 = bf16_lo(qraw[s][i]) * inv * gam[s][2 * i];
-        const float y1 = bf16_hi(qraw[s][i]) * inv * gam[s][2 * i + 1];
-        const float2 cs = rope_cs(a.rope, (d0 >> 1) + i, pt, ph, pw);
-        w[i] = pack_bf16((y0 * cs.x - y1 * cs.y) * a.scale_log2, (y0 * cs.y + y1 * cs.x) * a.scale_log2);
+        const float y0 = bf16_lo(x.raw[j][s][i]) * inv[j] * gam[2 * i];
+        const float y1 = bf16_hi(x.raw[j][s][i]) * inv[j] * gam[2 * i + 1];
+        w[i] = pack_bf16((y0 * cs[j][i].x - y1 * cs[j][i].y) * a.scale_log2,
+                         (y0 * cs[j][i].y + y1 * cs[j][i].x) * a.scale_log2);
       }
-      c.qreg[s] = as_bf16x8(q_ok ? w : (u32x4){0u, 0u, 0u, 0u});
+      // (a row past the call's end is all zeros, and stays so)
+      st.q[j][s] = as_bf16x8(x.rider[j] ? x.raw[j][s] : w);
     }
-  } else if (a.mode == 2 || rider) {  // prepared: Q'' as given
-#pragma unroll
-    for (int s = 0; s < 8; ++s) c.qreg[s] = as_bf16x8(qraw[s]);
-  } else {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      u32x4 w;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        w[i] = pack_bf16(bf16_lo(qraw[s][i]) * a.scale_log2, bf16_hi(qraw[s][i]) * a.scale_log2);
-      c.qreg[s] = as_bf16x8(w);
-    }
+  }
+}
+
+template <int kQT, bool kPrepared>
+__device__ __forceinline__ void video_segment(const AttnArgs& a, const VideoSeg& sg, VideoStream& s, int wave) {
+  const int wrow = sg.q_lo + wave * 16 * kQT;
+  VideoState<kQT> st;
+  {
+    RawQueries<kQT> raw;
+    fetch_queries<kQT, kPrepared>(a, sg, wrow, s.lane, raw);
+    prepare_rows<kQT, kPrepared>(a, raw, s.lane >> 4, st);
   }
 
   // ---- softmax shift ----
@@ -1066,197 +1165,140 @@ __device__ __forceinline__ void video_segment(const AttnArgs& a, const VideoSeg&
   // serves as the exp2 shift as it stands: p = exp2(s - B_q) <= 1, with no
   // running maximum and no rescale of O.  The row's largest p is at least
   // 2^(-2 B_q), so for B_q <= kShiftBoundMax every weight above 2^-46 of the
-  // row maximum stays a normal bf16/fp32 number.  Otherwise the running
-  // maximum is raised lazily: only when a 32-key tile exceeds it by more than
-  // kLazyTau (p then stays below 2^kLazyTau), which makes the O rescale rare.
+  // row maximum stays a normal bf16/fp32 number.  Above that the shift is
+  // B_q - kShiftBelowBound: p <= 2^16, and the same holds as long as the row's
+  // largest logit is at most kShiftReach below the shift, which the range's
+  // first keys show in all but extreme cases; otherwise the range runs under a
+  // running maximum.
+  float kn2 = 0.f;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, o));
-  float qn2 = 0.f;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    const u32x4 w = __builtin_bit_cast(u32x4, c.qreg[s]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qn2 += bf16_lo(w[i]) * bf16_lo(w[i]) + bf16_hi(w[i]) * bf16_hi(w[i]);
+  for (int k = 0; k < 2; ++k) {
+    const int idx = 64 * k + s.lane;
+    if (idx >= s.at && idx < s.at + sg.n) kn2 = fmaxf(kn2, s.kn2[k]);
   }
-  qn2 += __shfl_xor(qn2, 32);
-  const float bound = sqrtf(qn2 * kn2);
-  const bool fixed_shift = a.fixed_shift != 0 && __all(bound <= kShiftBoundMax);
+  for (int k = max(s.at, 128) + s.lane; k < s.at + sg.n; k += 64)
+    kn2 = fmaxf(kn2, a.knorm2[stream_entry(s, k) >> 7]);
+  kn2 = wave_max(kn2);
+  bool small = true;
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) {
+    float qn2 = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) qn2 = norm2_words(__builtin_bit_cast(u32x4, st.q[j][t]), qn2);
+    const float bound = sqrtf(pair_sum<32>(pair_sum<16>(qn2)) * kn2);
+    small = small && bound <= kShiftBoundMax;
+    st.m[j] = bound <= kShiftBoundMax ? bound : bound - kShiftBelowBound;
+  }
+  st.verify = !__all(small);
+  st.in_reach = true;
+  pin_queries(st);
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) {
+    const float neg = -st.m[j];
+    st.s_init[j] = (f32x4){neg, neg, neg, neg};
+  }
+  st.ones = (u32x4){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  asm volatile("" : "+v"(st.ones));
 
-  // ---- main loop over this segment's pages ----
-  VideoState st;
+  // ---- the segment's pages ----
+  if (s.at == 0) wait_dma_all_but_last_page();
+  const int end = s.at + sg.n;
+  const uint32_t stage0 = s.stage;
+  const int valid0 = static_cast<int>(s.valid & 0xffu);
+  video_iter<kQT, true>(st, s);
+  const bool running = a.fixed_shift == 0 || !st.in_reach;
+  // (one-armed branches in turn: of an if-else the compiler keeps both arms'
+  // accumulators)
+  if (running) {  // the first page once more (its stage is intact), then the rest
+    mfma_drain();
+    // (an opaque zero: 144 registers of constant zeros would be set up ahead of
+    // the segment loop and kept)
+    const float zero = __int_as_float(opaque(0));
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int j = 0; j < kQT; ++j) {
+      st.m[j] = kNegInf;
+      st.l[j] = (f32x4){zero, zero, zero, zero};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) st.o[t][r] = 0.f;
-  st.m_run = fixed_shift ? bound : 0.f;
-  st.l_run = 0.f;
-  st.first = true;
+      for (int dt = 0; dt < 8; ++dt) st.o[dt][j] = (f32x4){zero, zero, zero, zero};
+    }
+    uint32_t stage = stage0;
+    for (int n_valid = valid0;;) {
+      video_page_running_max<kQT>(st, s, stage, n_valid);
+      wait_dma_all_but_last_page();
+      if (s.at == end) break;
+      page_barrier();
+      issue_page(s, s.c);
+      stage = s.stage;
+      n_valid = static_cast<int>(s.valid & 0xffu);
+      stream_advance(s);
+    }
+  }
+  while (s.at < end) video_iter<kQT, false>(st, s);
+  if (!running) video_flush<kQT>(st, s);
+  if (s.at == s.n) wait_dma_all();  // no direct load may still be writing this workgroup's LDS when it exits
 
-  if (p_begin < p_end) wait_dma_all_but_last_page();
-  if (c.active && fixed_shift) {
-    if (p_begin < p_end) {
-      PipeState ps;
-      f32x16 s_init;
+  // ---- epilogue: lane holds O^T[16 dt + 4 g + r][q] ----
+  const int lane_e = opaque(s.lane), ge = lane_e >> 4, ie = lane_e & 15;
+  const bool riders = a.n_rq > 0 && wrow + 16 * kQT > a.rq_row0;
+  // bf16: the output itself, or the partial of a key range: the
+  // softmax-normalised O (a convex combination of V rows, so bf16 keeps its
+  // range; the merge adds at most one more bf16 rounding of the output's size)
+  // and its fp32 log-sum-exp.
+  const int64_t part_row = (static_cast<int64_t>(sg.seg) * a.num_heads + sg.head) * a.n_q;
+  uint16_t* const base = sg.whole ? a.out + sg.head * a.out_head_stride
+                                  : reinterpret_cast<uint16_t*>(a.part_o) + part_row * kHeadDim;
+  const int64_t stride = sg.whole ? a.out_tok_stride : kHeadDim;
+  uint16_t* const op = base + (wrow + ie) * stride + 16 * (ge & 1) + 8 * (ge >> 1);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s_init[r] = -st.m_run;
-      video_iter<0, true>(c, st, ps, s_init, p_begin, p_end);
-      for (int pi = p_begin + 1; pi < p_end; pi += 5) {
-        video_iter<1, false>(c, st, ps, s_init, pi, p_end);
-        if (pi + 1 < p_end) video_iter<2, false>(c, st, ps, s_init, pi + 1, p_end);
-        if (pi + 2 < p_end) video_iter<3, false>(c, st, ps, s_init, pi + 2, p_end);
-        if (pi + 3 < p_end) video_iter<4, false>(c, st, ps, s_init, pi + 3, p_end);
-        if (pi + 4 < p_end) video_iter<0, false>(c, st, ps, s_init, pi + 4, p_end);
+  for (int j = 0; j < kQT; ++j) {
+    const int row = wrow + 16 * j + ie;
+    const float l = st.l[j][0];
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    const float lse = l > 0.f ? st.m[j] + __log2f(l) : kNegInf;
+    if (riders) {  // always a partial, fp32, for the rider rows' own merge
+      const int q = row - a.rq_row0;
+      if (q >= 0 && q < a.n_rq) {
+        const int64_t prow = (static_cast<int64_t>(sg.seg) * a.num_heads + sg.head) * a.n_rq + q;
+        float* po = a.rpart_o + prow * kHeadDim + 4 * ge;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4*>(po + 16 * dt) = st.o[dt][j] * inv;
+        if (ge == 0) a.rpart_lse[prow] = lse;
       }
-      video_flush(c, st, ps, (p_end - 1 - p_begin) % kStages);
     }
-  } else if (c.active) {
-    for (int pi = p_begin; pi < p_end; pi += 5) {
-      video_page<true, 0>(c, st, pi, p_end);
-      if (pi + 1 < p_end) video_page<true, 1>(c, st, pi + 1, p_end);
-      if (pi + 2 < p_end) video_page<true, 2>(c, st, pi + 2, p_end);
-      if (pi + 3 < p_end) video_page<true, 3>(c, st, pi + 3, p_end);
-      if (pi + 4 < p_end) video_page<true, 4>(c, st, pi + 4, p_end);
+    // Lane groups trade halves of two neighbouring d tiles, so that each lane
+    // writes 16 bytes: lane group g of (x[0], x[1]) -> groups (0, 2): d tile
+    // dt, (1, 3): dt + 1.
+    u32x4 w[4];
+#pragma unroll
+    for (int dt = 0; dt < 8; dt += 2) {
+      uint32_t x[2][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4 v = st.o[dt + h][j] * inv;
+        x[h][0] = pack_bf16(v[0], v[1]);
+        x[h][1] = pack_bf16(v[2], v[3]);
+      }
+      const auto w0 = __builtin_amdgcn_permlane16_swap(x[0][0], x[1][0], false, false);
+      const auto w1 = __builtin_amdgcn_permlane16_swap(x[0][1], x[1][1], false, false);
+      w[dt >> 1] = (u32x4){w0[0], w1[0], w0[1], w1[1]};
     }
-  } else {
-    for (int pi = p_begin; pi < p_end; pi += 5) {
-      video_page_stage_only<0>(c, pi, p_end);
-      if (pi + 1 < p_end) video_page_stage_only<1>(c, pi + 1, p_end);
-      if (pi + 2 < p_end) video_page_stage_only<2>(c, pi + 2, p_end);
-      if (pi + 3 < p_end) video_page_stage_only<3>(c, pi + 3, p_end);
-      if (pi + 4 < p_end) video_page_stage_only<4>(c, pi + 4, p_end);
+    if (row < sg.q_hi) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) *reinterpret_cast<u32x4*>(op + 16 * j * stride + 32 * n) = w[n];
+      if (!sg.whole && ge == 0) a.part_lse[part_row + row] = lse;
     }
   }
-  // no direct load may still be writing this workgroup's LDS when it exits
-  wait_dma_all();
-
-  // ---- epilogue: lane holds O^T[32t + 8g + 4h + i][q], g = r/4, i = r%4 ----
-  const float l_tot = st.l_run + __shfl_xor(st.l_run, 32);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if (rider) {  // always a partial, fp32, for the rider rows' own merge
-    if (!q_ok) return;
-    const int64_t row = (static_cast<int64_t>(sg.seg) * a.num_heads + head) * a.n_rq + q;
-    float* po = a.rpart_o + row * kHeadDim;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 w = {st.o[t][4 * g] * inv, st.o[t][4 * g + 1] * inv, st.o[t][4 * g + 2] * inv,
-                         st.o[t][4 * g + 3] * inv};
-        *reinterpret_cast<f32x4*>(po + 32 * t + 8 * g + 4 * half) = w;
-      }
-    if (half == 0) a.rpart_lse[row] = l_tot > 0.f ? st.m_run + __log2f(l_tot) : kNegInf;
-    return;
-  }
-  if (sg.n_seg == 1) {
-    if (!q_ok) return;
-    uint16_t* op = a.out + q * a.out_tok_stride + head * a.out_head_stride;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d0 = 32 * t + 8 * g + 4 * half;
-        u32x2 w;
-        w[0] = pack_bf16(st.o[t][4 * g] * inv, st.o[t][4 * g + 1] * inv);
-        w[1] = pack_bf16(st.o[t][4 * g + 2] * inv, st.o[t][4 * g + 3] * inv);
-        *reinterpret_cast<u32x2*>(op + d0) = w;
-      }
-    return;
-  }
-  // Partial of a key range: the softmax-normalised O rounded to bf16 (a
-  // convex combination of V rows, so bf16 keeps its range; the merge adds at
-  // most one more bf16 rounding of the output's size) and its fp32
-  // log-sum-exp.  Half the bytes of fp32 partials, written here and read by
-  // the combine kernel.
-  if (!q_ok) return;
-  const int64_t row = (static_cast<int64_t>(sg.seg) * a.num_heads + head) * a.n_q + q;
-  uint16_t* po = reinterpret_cast<uint16_t*>(a.part_o) + row * kHeadDim;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int d0 = 32 * t + 8 * g + 4 * half;
-      u32x2 w;
-      w[0] = pack_bf16(st.o[t][4 * g] * inv, st.o[t][4 * g + 1] * inv);
-      w[1] = pack_bf16(st.o[t][4 * g + 2] * inv, st.o[t][4 * g + 3] * inv);
-      *reinterpret_cast<u32x2*>(po + d0) = w;
-    }
-  if (half == 0) a.part_lse[row] = l_tot > 0.f ? st.m_run + __log2f(l_tot) : kNegInf;
 }
 
-// The call's query classes, read in place from the kernel arguments (the
-// kernel's only argument is the AttnArgs; indexing the by-value argument at a
-// run-time class would make the compiler copy it to private memory).
+// The class table, read in place from the kernel arguments (the kernel's only
+// argument is the AttnArgs; indexing the by-value argument at a run-time class
+// would make the compiler copy it to private memory).
 typedef const __attribute__((address_space(4))) AttnClass* const_class_table;
 __device__ __forceinline__ const_class_table class_table() {
   const __attribute__((address_space(4))) char* seg =
       (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
   return (const_class_table)(seg + offsetof(AttnArgs, cls));
 }
-
-__device__ __forceinline__ void rider_pages_wave(const AttnArgs& a, int head, int range0, int k, int n);
-
-__global__ __launch_bounds__(kVideoWaves * 64) void unit_attn_kernel(const AttnArgs a) {
-  // Work decode.  Each query class (the rows of one unit's queries, with the
-  // pages its mask leaves visible) owns a block of workgroups: n_groups
-  // groups of n_qtiles workgroups; group g takes a contiguous share of the
-  // class's (head, page) units in head-major order (VideoPartition: even
-  // shares of pages plus a cost per head started), one workgroup per query
-  // tile, so the work fits a single round, and a share that crosses a head
-  // boundary is processed as two segments.  Workgroups are dispatched
-  // round-robin over the 8 XCDs; renumber so that consecutive work items
-  // (the query tiles of a group, which read the same pages at the same time,
-  // and neighbouring groups) run on one XCD and share its L2.
-  const int nblk = gridDim.x, bid = blockIdx.x;
-  const int xcd = bid & 7, per = nblk >> 3, rem = nblk & 7;
-  const int item = xcd * per + min(xcd, rem) + (bid >> 3);
-  const const_class_table tab = class_table();
-  int ci = 0;
-  for (int k = 1; k < a.n_classes; ++k)
-    if (item >= tab[k].wg0) ci = k;
-  const int local = item - tab[ci].wg0;
-  const int n_qtiles = tab[ci].n_qtiles;
-  const int q0 = tab[ci].q0, q_hi = q0 + tab[ci].n_q;
-  const int page0 = tab[ci].page0;
-  const int q_lo = q0 + (local % n_qtiles) * kVideoQTile;
-  const int64_t group = local / n_qtiles;
-  const int64_t n_pages = tab[ci].n_pages;
-  if (n_pages == 0) {  // nothing visible: one empty segment per head, output 0
-    if (group < a.num_heads)
-      video_segment(a, VideoSeg{static_cast<int>(group), 0, 0, 0, 1, q_lo, q_hi}, true);
-    return;
-  }
-  const VideoPartition part{a.num_heads, n_pages, a.seg_cost, tab[ci].n_groups};
-  const int64_t lo = video_group_lo(part, group), hi = video_group_lo(part, group + 1);
-  // The rider rows' own pages: in the last query tile's workgroup of the
-  // group that holds a head's last page, the waves without rows of their
-  // own (the last rx_waves of the 8) attend them for that head before they
-  // join the page loop (where such waves only stage pages), as key ranges
-  // after the head's ranges of the shared pages.
-  if (a.rx_pages > 0 && local % n_qtiles == n_qtiles - 1 && lo < hi) {
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    const int k = wave - (kVideoWaves - a.rx_waves);
-    if (k >= 0) {
-      for (int64_t head = lo / n_pages; head <= (hi - 1) / n_pages; ++head) {
-        const int64_t h0 = head * n_pages;
-        if (video_group_of(part, h0 + n_pages - 1) != group) continue;
-        rider_pages_wave(a, static_cast<int>(head), static_cast<int>(group - video_group_of(part, h0) + 1), k,
-                         a.rx_waves);
-      }
-    }
-  }
-  bool first = true;
-  for (int64_t x = lo; x < hi; first = false) {
-    const int64_t head = x / n_pages, h0 = head * n_pages;
-    const int64_t x_end = min(hi, h0 + n_pages);
-    const int64_t g_first = video_group_of(part, h0);
-    const int64_t g_last = video_group_of(part, h0 + n_pages - 1);
-    const VideoSeg sg{static_cast<int>(head), page0 + static_cast<int>(x - h0), page0 + static_cast<int>(x_end - h0),
-                      static_cast<int>(group - g_first), static_cast<int>(g_last - g_first + 1), q_lo, q_hi};
-    video_segment(a, sg, first);
-    x = x_end;
-  }
-}
-
 // ------------------------------------------------------------------------- //
 // audio_attn: the few audio queries, memory-bound.  A workgroup of 4 waves
 // takes one (head, 16-query tile, key range); wave w streams pages w, w + 4,
@@ -1274,11 +1316,6 @@ __global__ __launch_bounds__(kVideoWaves * 64) void unit_attn_kernel(const AttnA
 // that accumulator registers r of tiles 2c and 2c + 1 in lane group g are
 // keys 32 c + 8 g + 0..7: exactly the B operand of the P*V MFMA of key chunk c.
 // ------------------------------------------------------------------------- //
-// Row m (lane index i) of key tile t: the key it holds.
-__device__ __forceinline__ int audio_key(int t, int m) {
-  return 32 * (t >> 1) + 8 * (m >> 2) + 4 * (t & 1) + (m & 3);
-}
-
 // Loads of one page's K operands, k[t][s] = K[key(t, i)][32 s + 8 g .. + 8],
 // and V^T operands, v[dt][c] = V^T[16 dt + i][32 c + 8 g .. + 8].  Rows and
 // columns past n_valid are read from the 1 KB zero block instead (a cache
@@ -1307,6 +1344,69 @@ __device__ __forceinline__ void audio_load_v(u32x4 (&v)[8][2], const uint16_t* v
   }
 }
 
+// S^T of one page's four key tiles.
+__device__ __forceinline__ void audio_scores(const u32x4 (&kreg)[4][4], const bf16x8 (&qreg)[4], f32x4 (&sacc)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    sacc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      sacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kreg[t][s]), qreg[s], sacc[t], 0, 0, 0);
+  }
+}
+
+// Softmax weights of one page (sacc, masked past n_valid here) as bf16 words
+// pw (word c of chunk c: keys 32 c + 8 g + 0..7), with the running maximum,
+// the row sum (over the same bf16 values the MFMAs consume) and O kept up to
+// date.
+__device__ __forceinline__ void audio_softmax(f32x4 (&sacc)[4], int n_valid, bool fixed_shift, int g, u32x4 (&pw)[2],
+                                              f32x4 (&o)[8], float& m_run, float& l_run) {
+  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+  if (n_valid < kPageTokens) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (audio_key(t, 4 * g + r) >= n_valid) sacc[t][r] = kNegInf;
+  }
+  float alpha = 1.f;
+  if (!fixed_shift) {
+    float mx = kNegInf;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) mx = fmaxf(mx, fmaxf(fmaxf(sacc[t][0], sacc[t][1]), fmaxf(sacc[t][2], sacc[t][3])));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m_run, mx);
+    alpha = m_new == kNegInf ? 1.f : fast_exp2(m_run - m_new);
+    m_run = m_new;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+  }
+  const float m_use = m_run == kNegInf ? 0.f : m_run;
+  float psum = 0.f;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f32x4& sc = sacc[2 * c + h];
+      const uint32_t w0 = pack_bf16(fast_exp2(sc[0] - m_use), fast_exp2(sc[1] - m_use));
+      const uint32_t w1 = pack_bf16(fast_exp2(sc[2] - m_use), fast_exp2(sc[3] - m_use));
+      pw[c][2 * h] = w0;
+      pw[c][2 * h + 1] = w1;
+      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w0), ones, psum, false);
+      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w1), ones, psum, false);
+    }
+  l_run = l_run * alpha + psum;
+}
+
+__device__ __forceinline__ void audio_pv(const u32x4 (&vreg)[8][2], const u32x4 (&pw)[2], f32x4 (&o)[8]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vreg[dt][c]), as_bf16x8(pw[c]), o[dt], 0, 0, 0);
+}
+
 // The page loop of the audio path, one wave: pages p_begin, p_begin + step,
 // ... (< p_end) of the list, whose first page's operands kreg and vreg hold
 // on entry.  Accumulates O^T (o), the running maximum and the row sum of the
@@ -1324,137 +1424,36 @@ __device__ __forceinline__ void audio_page_loop(const_page_list pages, int p_beg
                                                 f32x4 (&o)[8], float& m_run, float& l_run) {
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
   for (int pi = p_begin; pi < p_end; pi += step) {
     const int n_valid = pages[pi].y;
     int2 nxt = make_int2(0, 0);  // past the last page: zeros
     if (pi + step < p_end) nxt = make_int2(pages[pi + step].x, pages[pi + step].y);
-    // S^T of the page's four key tiles
     f32x4 sacc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      sacc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        sacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kreg[t][s]), qreg[s], sacc[t], 0, 0, 0);
-    }
+    audio_scores(kreg, qreg, sacc);
     audio_load_k(kreg, kpool + nxt.x * page_stride, zeros, nxt.y, g, i16, lane);
-    if (n_valid < kPageTokens) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (audio_key(t, 4 * g + r) >= n_valid) sacc[t][r] = kNegInf;
-    }
-    float alpha = 1.f;
-    if (!fixed_shift) {
-      float mx = kNegInf;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) mx = fmaxf(mx, fmaxf(fmaxf(sacc[t][0], sacc[t][1]), fmaxf(sacc[t][2], sacc[t][3])));
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float m_new = fmaxf(m_run, mx);
-      alpha = m_new == kNegInf ? 1.f : fast_exp2(m_run - m_new);
-      m_run = m_new;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
-    }
-    const float m_use = m_run == kNegInf ? 0.f : m_run;
-    // P in bf16 (word c of chunk c: keys 32 c + 8 g + 0..7); the row sum is
-    // taken over the same bf16 values the MFMAs consume
     u32x4 pw[2];
-    float psum = 0.f;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x4& sc = sacc[2 * c + h];
-        const uint32_t w0 = pack_bf16(fast_exp2(sc[0] - m_use), fast_exp2(sc[1] - m_use));
-        const uint32_t w1 = pack_bf16(fast_exp2(sc[2] - m_use), fast_exp2(sc[3] - m_use));
-        pw[c][2 * h] = w0;
-        pw[c][2 * h + 1] = w1;
-        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w0), ones, psum, false);
-        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w1), ones, psum, false);
-      }
-    l_run = l_run * alpha + psum;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vreg[dt][c]), as_bf16x8(pw[c]), o[dt], 0, 0, 0);
+    audio_softmax(sacc, n_valid, fixed_shift, g, pw, o, m_run, l_run);
+    audio_pv(vreg, pw, o);
     audio_load_v(vreg, vpool + nxt.x * page_stride, zeros, nxt.y, g, i16, lane);
   }
 }
 
-// The rider rows over their own pages (entries rx_page0 .. rx_page0 + rx_pages
-// of the page list) for one head, inside the video kernel: the audio path's
-// page loop on all 8 waves (wave w takes pages w, w + 8, ...), 16 rider rows
-// at a time, merged across the waves through the (then idle) LDS stages and
-// written as key range `range` of the rows' fp32 partials.
-// The rider rows over their own pages (entries rx_page0 .. rx_page0 + rx_pages
-// of the page list) for one head, by one wave of the video kernel that has no
-// rows of its own: the audio path's page loop over pages k, k + n, ... of
-// them (wave k of n such waves), 16 rider rows at a time, each written as a
-// key range of its own (range0 + k) of the rows' fp32 partials.  No LDS and
-// no barrier: the wave does this before its first page barrier, while the
-// waves with rows run their first segment's prologue.
-__device__ __forceinline__ void rider_pages_wave(const AttnArgs& a, int head, int range0, int k, int n) {
-  const int lane = threadIdx.x & 63;
-  const int g = lane >> 4, i16 = lane & 15;
-  const_page_list pages = page_list(a);
-  const int64_t page_stride = static_cast<int64_t>(a.num_heads) * kPageHeadElems;
-  const uint16_t* kpool = a.kpool + head * kPageHeadElems;
-  const uint16_t* vpool = a.vpool + head * kPageHeadElems;
-  const int p_begin = a.rx_page0 + k, p_end = a.rx_page0 + a.rx_pages;
-  const int64_t row0 = (static_cast<int64_t>(range0 + k) * a.num_heads + head) * a.n_rq;
-  for (int q0 = 0; q0 < a.n_rq; q0 += kAudioQTile) {
-    u32x4 kreg[4][4], vreg[8][2];
-    {
-      int2 pg = make_int2(0, 0);
-      if (p_begin < p_end) pg = make_int2(pages[p_begin].x, pages[p_begin].y);
-      audio_load_k(kreg, kpool + pg.x * page_stride, a.zeros, pg.y, g, i16, lane);
-      audio_load_v(vreg, vpool + pg.x * page_stride, a.zeros, pg.y, g, i16, lane);
-    }
-    const int q = q0 + i16;
-    const bool q_ok = q < a.n_rq;
-    bf16x8 qreg[4];
-    const uint16_t* qp = a.rq + q * a.rq_tok_stride + head * a.rq_head_stride + 8 * g;
+// The softmax shift bound of the audio path: |Q''_q| times the largest key
+// norm (squared: kn2, the lane's part of the pages), the same in all lane
+// groups of a row.
+__device__ __forceinline__ float audio_bound(const bf16x8 (&qreg)[4], float kn2) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-      qreg[s] = as_bf16x8(q_ok ? *reinterpret_cast<const u32x4*>(qp + 32 * s) : (u32x4){0u, 0u, 0u, 0u});
-    // softmax shift as in the audio kernel, over the wave's pages
-    float kn2 = 0.f;
-    for (int pi = p_begin + n * lane; pi < p_end; pi += 64 * n)
-      kn2 = fmaxf(kn2, a.knorm2[static_cast<int64_t>(pages[pi].x) * a.num_heads + head]);
+  for (int off = 1; off < 64; off <<= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, off));
+  float qn2 = 0.f;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, off));
-    float qn2 = 0.f;
+  for (int s = 0; s < 4; ++s) {
+    const u32x4 w = __builtin_bit_cast(u32x4, qreg[s]);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const u32x4 w = __builtin_bit_cast(u32x4, qreg[s]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) qn2 += bf16_lo(w[j]) * bf16_lo(w[j]) + bf16_hi(w[j]) * bf16_hi(w[j]);
-    }
-    qn2 += __shfl_xor(qn2, 16);
-    qn2 += __shfl_xor(qn2, 32);
-    const float bound = sqrtf(qn2 * kn2);
-    const bool fixed_shift = a.fixed_shift != 0 && __all(bound <= kShiftBoundMax);
-    float m_run = fixed_shift ? bound : kNegInf, l_run = 0.f;
-    f32x4 o[8];
-    audio_page_loop(pages, p_begin, p_end, n, kpool, vpool, page_stride, a.zeros, qreg, fixed_shift, kreg, vreg,
-                    g, i16, lane, o, m_run, l_run);
-    // lane holds O^T[16 dt + 4 g + r][q] of the wave's pages
-    float l_w = l_run + __shfl_xor(l_run, 16);
-    l_w += __shfl_xor(l_w, 32);
-    if (q_ok) {
-      const float inv = l_w > 0.f ? 1.0f / l_w : 0.f;
-      float* po = a.rpart_o + (row0 + q) * kHeadDim;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
-        *reinterpret_cast<f32x4*>(po + 16 * dt + 4 * g) = o[dt] * inv;
-      if (g == 0) a.rpart_lse[row0 + q] = l_w > 0.f ? m_run + __log2f(l_w) : kNegInf;
-    }
+    for (int k = 0; k < 4; ++k) qn2 += bf16_lo(w[k]) * bf16_lo(w[k]) + bf16_hi(w[k]) * bf16_hi(w[k]);
   }
+  qn2 += __shfl_xor(qn2, 16);
+  qn2 += __shfl_xor(qn2, 32);
+  return sqrtf(qn2 * kn2);
 }
 
 __global__ __launch_bounds__(256, 2) void audio_attn_kernel(const AttnArgs a) {
@@ -1544,18 +1543,7 @@ __global__ __launch_bounds__(256, 2) void audio_attn_kernel(const AttnArgs a) {
   float kn2 = 0.f;
   for (int pi = p_begin + 4 * lane; pi < p_end; pi += 256)
     kn2 = fmaxf(kn2, a.knorm2[static_cast<int64_t>(pages[pi].x) * a.num_heads + head]);
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, off));
-  float qn2 = 0.f;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const u32x4 w = __builtin_bit_cast(u32x4, qreg[s]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) qn2 += bf16_lo(w[k]) * bf16_lo(w[k]) + bf16_hi(w[k]) * bf16_hi(w[k]);
-  }
-  qn2 += __shfl_xor(qn2, 16);
-  qn2 += __shfl_xor(qn2, 32);
-  const float bound = sqrtf(qn2 * kn2);
+  const float bound = audio_bound(qreg, kn2);
   const bool fixed_shift = a.fixed_shift != 0 && __all(bound <= kShiftBoundMax);
   float m_run = fixed_shift ? bound : kNegInf, l_run = 0.f;
 
@@ -1608,6 +1596,275 @@ __global__ __launch_bounds__(256, 2) void audio_attn_kernel(const AttnArgs a) {
 }
 
 // ------------------------------------------------------------------------- //
+// The rider rows' own pages (entries rx_page0 .. of the page list, visible to
+// them only), inside the video kernel: the last wave of the last query tile's
+// workgroups attends them with the audio path's arithmetic; each of a head's
+// first rx_ranges ranges takes its part of them and writes it as a key range of
+// its own (after the head's ranges of the shared pages) of the rows' fp32
+// partials.  A wave without rows does so between the page loads it issues
+// anyway: one page's registers are requested in one iteration of the stream
+// and consumed in the next (the request in the same iteration as a computation
+// would hold up the page barrier), so the other waves never wait for it.  (With
+// three such waves attending three pages each ahead of their first page
+// barrier, the barrier waited 7 us.)  A wave with rows does it after its
+// segments: a page or two, against a launch of the audio kernel (6 us).
+// ------------------------------------------------------------------------- //
+struct RiderWork {
+  int head, range, p0, np;  // pages [p0, p0 + np) of the list
+  int item, n_items;        // item: (16-row subtile, page), the pages innermost
+  bool loaded;              // the item's operands are requested
+  bool fixed_shift;
+  float m, l;
+  u32x4 k[4][4], v[8][2];
+  f32x4 o[8];
+  bf16x8 q[4];
+};
+
+__device__ __forceinline__ void rider_request(const AttnArgs& a, RiderWork& w, int lane) {
+  const int g = lane >> 4, i16 = lane & 15;
+  const const_page_list pages = page_list(a);
+  const int per = max(w.np, 1), sub = w.item / per, pg = w.item - sub * per;
+  if (pg == 0) {
+    const int q = 16 * sub + i16;
+    const bool ok = q < a.n_rq;
+    const uint16_t* qp = a.rq + q * a.rq_tok_stride + w.head * a.rq_head_stride + 8 * g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      w.q[s] = as_bf16x8(ok ? *reinterpret_cast<const u32x4*>(qp + 32 * s) : (u32x4){0u, 0u, 0u, 0u});
+    float kn2 = 0.f;
+    for (int pi = w.p0 + lane; pi < w.p0 + w.np; pi += 64)
+      kn2 = fmaxf(kn2, a.knorm2[static_cast<int64_t>(pages[pi].x) * a.num_heads + w.head]);
+    const float bound = audio_bound(w.q, kn2);
+    w.fixed_shift = a.fixed_shift != 0 && __all(bound <= kShiftBoundMax);
+    w.m = w.fixed_shift ? bound : kNegInf;
+    w.l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) w.o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  int2 p = make_int2(0, 0);  // no page: zeros
+  if (pg < w.np) p = make_int2(pages[w.p0 + pg].x, pages[w.p0 + pg].y);
+  const int64_t tile = (static_cast<int64_t>(p.x) * a.num_heads + w.head) * kPageHeadElems;
+  audio_load_k(w.k, a.kpool + tile, a.zeros, p.y, g, i16, lane);
+  audio_load_v(w.v, a.vpool + tile, a.zeros, p.y, g, i16, lane);
+  w.loaded = true;
+}
+
+__device__ __forceinline__ void rider_compute(const AttnArgs& a, RiderWork& w, int lane) {
+  const int g = lane >> 4, i16 = lane & 15;
+  const const_page_list pages = page_list(a);
+  const int per = max(w.np, 1), sub = w.item / per, pg = w.item - sub * per;
+  f32x4 sacc[4];
+  u32x4 pw[2];
+  audio_scores(w.k, w.q, sacc);
+  audio_softmax(sacc, pg < w.np ? pages[w.p0 + pg].y : 0, w.fixed_shift, g, pw, w.o, w.m, w.l);
+  audio_pv(w.v, pw, w.o);
+  if (pg == per - 1) {  // lane holds O^T[16 dt + 4 g + r][q]
+    float l = w.l + __shfl_xor(w.l, 16);
+    l += __shfl_xor(l, 32);
+    const int q = 16 * sub + i16;
+    if (q < a.n_rq) {
+      const int64_t row = (static_cast<int64_t>(w.range) * a.num_heads + w.head) * a.n_rq + q;
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+      float* po = a.rpart_o + row * kHeadDim + 4 * g;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4*>(po + 16 * dt) = w.o[dt] * inv;
+      if (g == 0) a.rpart_lse[row] = l > 0.f ? w.m + __log2f(l) : kNegInf;
+    }
+  }
+  ++w.item;
+  w.loaded = false;
+}
+
+// The rider rows' pages that range sg.seg of the n_seg of its head takes.
+__device__ __forceinline__ void rider_share(const AttnArgs& a, const VideoSeg& sg, int n_seg, RiderWork& w) {
+  const int parts = min(n_seg, a.rx_ranges);
+  w.item = 0;
+  w.n_items = 0;
+  w.loaded = false;
+  if (sg.seg >= parts) return;
+  w.head = sg.head;
+  w.range = n_seg + sg.seg;
+  w.p0 = a.rx_page0 + a.rx_pages * sg.seg / parts;
+  w.np = a.rx_page0 + a.rx_pages * (sg.seg + 1) / parts - w.p0;
+  w.n_items = ((a.n_rq + 15) / 16) * max(w.np, 1);
+}
+__device__ __forceinline__ void rider_rest(const AttnArgs& a, RiderWork& w, int lane) {
+  while (w.item < w.n_items) {
+    if (!w.loaded) rider_request(a, w, lane);
+    rider_compute(a, w, lane);
+  }
+}
+
+// A segment for a wave without query rows: it issues its share of the page
+// loads and attends the rider rows' pages (n_seg > 0: the head's ranges).
+__device__ __forceinline__ void video_idle_segment(const AttnArgs& a, const VideoSeg& sg, VideoStream& s, int n_seg) {
+  RiderWork w;
+  w.item = w.n_items = 0;
+  w.loaded = false;
+  if (n_seg > 0) rider_share(a, sg, n_seg, w);
+  if (s.at == 0) wait_dma_all_but_last_page();
+  for (int k = 0; k < sg.n; ++k) {
+    page_barrier();
+    if (w.item < w.n_items) {
+      if (w.loaded) rider_compute(a, w, s.lane);
+      else rider_request(a, w, s.lane);
+    }
+    issue_page(s, s.c);
+    const uint32_t e = stream_peek(s, min(s.at + 4, s.n - 1));
+    s.at += 1;
+    s.stage = ring_add(s.stage, 1);
+    set_load(s, e, ring_add(s.stage, 3), s.c);
+    wait_dma_all_but_last_page();
+    stream_reach(s);
+  }
+  rider_rest(a, w, s.lane);  // a short segment's
+}
+
+// The segment at stream offset k of group `group`'s share.
+__device__ __forceinline__ VideoPartition32 part_of(const __attribute__((address_space(4))) AttnClass& c) {
+  const auto& p = c.part;
+  return VideoPartition32{p.pages, p.cost, p.len, p.groups, p.quot, p.rem, p.fits,
+                          {p.by_pages.mul, p.by_pages.shift}, {p.by_stride.mul, p.by_stride.shift},
+                          {p.by_groups.mul, p.by_groups.shift}, {p.by_len.mul, p.by_len.shift}};
+}
+struct VideoWork {
+  VideoPartition32 part;
+  int group, q_lo, q_hi;
+};
+__device__ __forceinline__ VideoSeg video_seg(const VideoWork& w, const VideoStream& s, int k) {
+  const int x = s.lo + k;
+  const int head = static_cast<int>(fast_div(x, s.div_pages)), h0 = head * s.n_pages;
+  const int n = min(s.n - k, h0 + s.n_pages - x);
+  const int seg = x == h0 ? 0 : w.group - static_cast<int>(part_group_of(w.part, h0));
+  return VideoSeg{head, n, seg, w.q_lo, w.q_hi, x == h0 && n == s.n_pages};
+}
+
+// Ranges of a head (for the rider rows' partials).
+__device__ __forceinline__ int head_ranges(const VideoWork& w, const VideoStream& s, int head) {
+  const int h0 = head * s.n_pages;
+  return static_cast<int>(part_group_of(w.part, h0 + s.n_pages - 1) - part_group_of(w.part, h0)) + 1;
+}
+
+template <int kQT, bool kPrepared>
+__device__ __forceinline__ void video_wave(const AttnArgs& a, const VideoWork& w, VideoStream& s, int wave) {
+  stream_start(a, s);
+  while (s.at < s.n) video_segment<kQT, kPrepared>(a, video_seg(w, s, s.at), s, wave);
+}
+
+// The rider rows' pages for a wave with rows of its own, after its segments.
+__device__ __forceinline__ void rider_segments(const AttnArgs& a, const VideoWork& w, const VideoStream& s) {
+  for (int k = 0; k < s.n;) {
+    const VideoSeg sg = video_seg(w, s, k);
+    RiderWork r;
+    rider_share(a, sg, head_ranges(w, s, sg.head), r);
+    rider_rest(a, r, opaque(s.lane));
+    k += sg.n;
+  }
+}
+
+// Rows that see nothing: output 0.
+__device__ __forceinline__ void video_empty(const AttnArgs& a, int head, int q_lo, int q_hi) {
+  const int n = min(kVideoQTile, q_hi - q_lo) * (kHeadDim / 8);
+  for (int i = threadIdx.x; i < n; i += kVideoWaves * 64) {
+    const int64_t q = q_lo + i / (kHeadDim / 8);
+    *reinterpret_cast<u32x4*>(a.out + q * a.out_tok_stride + head * a.out_head_stride + 8 * (i % (kHeadDim / 8))) =
+        (u32x4){0u, 0u, 0u, 0u};
+  }
+}
+
+// kPrepared: the video queries come prepared (query mode 2).
+template <bool kPrepared>
+__device__ __forceinline__ void unit_attn(const AttnArgs& a) {
+  // Work decode.  Each query class (the rows of one unit's queries, with the
+  // pages its mask leaves visible) owns a block of workgroups: n_groups
+  // groups of n_qtiles workgroups; group g takes a contiguous share of the
+  // class's (head, page) units in head-major order (VideoPartition: even
+  // shares of pages plus a cost per head started), one workgroup per query
+  // tile, so the work fits a single round, and a share that crosses a head
+  // boundary is processed as several segments.  Workgroups are dispatched
+  // round-robin over the 8 XCDs; renumber so that consecutive work items
+  // (the query tiles of a group, which read the same pages at the same time,
+  // and neighbouring groups) run on one XCD and share its L2.  The divisions
+  // are multiplications by host-made reciprocals: with the partition's own
+  // integer divisions a workgroup spent 5 us before its first load.
+  const int nblk = gridDim.x, bid = blockIdx.x;
+  const int xcd = bid & 7, per = nblk >> 3, rem = nblk & 7;
+  const int item = xcd * per + min(xcd, rem) + (bid >> 3);
+  const const_class_table tab = class_table();
+  int ci = 0;
+  for (int k = 1; k < a.n_classes; ++k)
+    if (item >= tab[k].wg0) ci = k;
+  const int local = item - tab[ci].wg0;
+  const int n_qtiles = tab[ci].n_qtiles;
+  const int group = static_cast<int>(fast_div(local, FastDiv{tab[ci].by_qtiles.mul, tab[ci].by_qtiles.shift}));
+  const int qt = local - group * n_qtiles;
+  const int q0 = tab[ci].q0, q_hi = q0 + tab[ci].n_q;
+  const int q_lo = q0 + qt * kVideoQTile;
+  // rider rows follow the video rows (a single class then)
+  const int row_end = min(q_lo + kVideoQTile, a.n_rq > 0 ? a.rq_row0 + a.n_rq : q_hi);
+  const bool wide = video_wave_rows(row_end - q_lo) == 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+
+  VideoWork w;
+  w.group = group;
+  w.q_lo = q_lo;
+  w.q_hi = q_hi;
+  VideoStream s;
+  s.pages = page_list(a);
+  s.num_heads = a.num_heads;
+  s.n_pages = tab[ci].n_pages;
+  s.page0 = tab[ci].page0;
+  s.lane = lane;
+  s.kpool = a.kpool;
+  s.vpool = a.vpool;
+  s.at = 0;
+  s.stage = 0;
+  s.valid = 0;
+  if (s.n_pages == 0) {  // nothing visible: one group per head
+    if (group < a.num_heads) video_empty(a, group, q_lo, q_hi);
+    return;
+  }
+  w.part = part_of(tab[ci]);
+  s.div_pages = w.part.by_pages;
+  s.lo = static_cast<int>(part_group_lo(w.part, group));
+  s.n = static_cast<int>(part_group_lo(w.part, group + 1)) - s.lo;
+  if (s.n == 0) return;
+  // the list entries of the window are requested here and combined after the
+  // queries' loads are under way
+  stream_request(s);
+  {
+    // K block wave: row 4 wave + lane / 16 of key tile 0, position lane % 16
+    const int m = 4 * wave + (lane >> 4);
+    s.dma_k = 2 * k_tile_index(audio_key(0, m), 8 * ((lane & 15) ^ m));
+    // V^T block wave: row d = 8 wave + lane / 8, position lane % 8
+    const int d = 8 * wave + (lane >> 3);
+    s.dma_v = 2 * v_tile_index(8 * ((lane & 7) ^ ((d >> 1) & 7)), d);
+    const uint32_t lds = lds_offset(g_stages);
+    s.lds0 = __builtin_amdgcn_readfirstlane(lds + 1024u * wave);
+    const int g = lane >> 4, i16 = lane & 15;
+    s.k_read = lds + 256u * i16 + 16u * (g ^ i16);
+    s.v_read = lds + kStageV + 128u * i16 + 16u * (g ^ ((i16 >> 1) & 7));
+  }
+  const bool rx = a.rx_pages > 0 && qt == n_qtiles - 1 && wave == kVideoWaves - 1;
+  if (q_lo + wave * (wide ? 64 : 32) >= row_end) {
+    stream_start(a, s);
+    while (s.at < s.n) {
+      const VideoSeg sg = video_seg(w, s, s.at);
+      video_idle_segment(a, sg, s, rx ? head_ranges(w, s, sg.head) : 0);
+    }
+    wait_dma_all();
+    return;
+  }
+  if (wide) video_wave<4, kPrepared>(a, w, s, wave);
+  else video_wave<2, kPrepared>(a, w, s, wave);
+  if (rx) rider_segments(a, w, s);
+}
+
+#define WS_ONE_WAVE_PER_SIMD __launch_bounds__(kVideoWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ WS_ONE_WAVE_PER_SIMD void unit_attn_kernel(const AttnArgs a) { unit_attn<true>(a); }
+__global__ WS_ONE_WAVE_PER_SIMD void unit_attn_rows_kernel(const AttnArgs a) { unit_attn<false>(a); }
+
+// ------------------------------------------------------------------------- //
 // combine (audio key ranges): 16 threads per (head, query) row, 8 d each, 16
 // rows per block.  A thread reads the row's log-sum-exps, then requests the
 // 8 values of kMergeBatch ranges before using any (one memory round trip per
@@ -1626,8 +1883,8 @@ __device__ __forceinline__ void combine_block(const CombineArgs& a, int bid) {
   if (a.r_groups > 0) {  // the ranges the video kernel wrote for rider rows
     const VideoPartition part{a.num_heads, a.r_pages, a.seg_cost, a.r_groups};
     const int64_t h0 = static_cast<int64_t>(head) * a.r_pages;
-    n_splits += static_cast<int>(video_group_of(part, h0 + a.r_pages - 1) - video_group_of(part, h0) + 1) +
-                a.r_extra;  // and those of the rows' own pages
+    const int ranges = static_cast<int>(video_group_of(part, h0 + a.r_pages - 1) - video_group_of(part, h0) + 1);
+    n_splits += ranges + min(ranges, a.r_extra);  // and those of the rows' own pages
   }
   const int d0 = 8 * lane;
   const int64_t split_stride = static_cast<int64_t>(a.num_heads) * a.n_q;
@@ -1815,10 +2072,11 @@ hipError_t launch_kv_append(const AppendArgs& a, hipStream_t stream, hipEvent_t 
 
 hipError_t launch_unit_attention(const AttnArgs& a, hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
   const dim3 grid(a.n_wg), block(kVideoWaves * 64);
+  const auto kernel = a.mode == 2 ? unit_attn_kernel : unit_attn_rows_kernel;
   if (start || stop)
-    hipExtLaunchKernelGGL(unit_attn_kernel, grid, block, 0, stream, start, stop, 0, a);
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, a);
   else
-    hipLaunchKernelGGL(unit_attn_kernel, grid, block, 0, stream, a);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

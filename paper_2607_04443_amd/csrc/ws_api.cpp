@@ -58,13 +58,12 @@ using ws_internal::hip_fail;
 using ws::kMaxVideoSplits;
 // Blocks per CU of an append launch; each loops over the launch's tiles.
 constexpr int kAppendBlocksPerCu = 4;
-// Fewest waves without rows in the video call's last query tile (with the
-// audio rows) for the video kernel to attend the audio rows' own pages.
-constexpr int kRiderMinIdleWaves = 2;
 // Pages per key range of the audio kernel when the step's audio rows ride in
 // the video kernel and it walks only the audio-token pages (one page per
 // wave: measured 1.5 us faster per step than two).
 constexpr int kRiderPagesPerRange = 4;
+// Pages per range that a wave with rows of its own attends for the rider rows.
+constexpr int kRiderPagesPerBusyWave = 4;
 constexpr int kMaxAudioSplits = 512;
 using ws::kMaxAudioQ;
 
@@ -565,6 +564,8 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
       a.cls[k].n_qtiles = (a.cls[k].n_q + ws::kVideoQTile - 1) / ws::kVideoQTile;
       work += static_cast<int64_t>(a.cls[k].n_qtiles) * a.cls[k].n_pages;
     }
+    // forced splits keep equal ranges per head
+    const int32_t seg_cost = c->opt_video_splits > 0 ? 0 : kVideoSegCostPages;
     int64_t max_ranges = 1;
     int32_t wg = 0, total_groups = 0;
     merge = false;
@@ -576,6 +577,8 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
                           : static_cast<int>(std::max<int64_t>(cl.n_qtiles, c->num_cus * w / work));
       cl.n_groups = choose_video_groups(c, H, cl.n_qtiles, cl.n_pages, cus);
       cl.wg0 = wg;
+      cl.by_qtiles = ws::make_fast_div(cl.n_qtiles);
+      cl.part = ws::make_part32(ws::VideoPartition{H, std::max(cl.n_pages, 1), seg_cost, cl.n_groups});
       wg += cl.n_groups * cl.n_qtiles;
       total_groups += cl.n_groups;
       // ranges per head: exactly the forced split count, else at most
@@ -595,8 +598,7 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
     a.n_wg = wg;
     a.n_qtiles = 0;
     for (int k = 0; k < n_cls; ++k) a.n_qtiles += a.cls[k].n_qtiles;
-    // forced splits keep equal ranges per head
-    a.seg_cost = c->opt_video_splits > 0 ? 0 : kVideoSegCostPages;
+    a.seg_cost = seg_cost;
     a.n_splits = 1;
     splits = total_groups;
   }
@@ -658,6 +660,15 @@ ws_status attention_impl(bool audio, const void* q, int64_t q_tok_stride, int64_
   return timing_mark(c, slot, 2, stream);
 }
 
+// Audio partial rows (fp32 O and log-sum-exp) the static workspace holds next to
+// the video call's partials.
+int64_t static_audio_rows(const AttnPlan& pv) {
+  const int64_t rv = pv.part_rows;
+  const int64_t left = static_cast<int64_t>(ws::kStaticScratchBytes) - 4 * 256 -
+                       rv * static_cast<int64_t>(ws::kHeadDim * sizeof(uint16_t) + sizeof(float));
+  return std::max<int64_t>(left, 0) / static_cast<int64_t>((ws::kHeadDim + 1) * sizeof(float));
+}
+
 // Puts both calls' split-KV partials into the static workspace: video bf16
 // O rows, audio fp32 O rows, and their fp32 log-sum-exp, each region
 // 256-byte aligned.  Fails (before anything is enqueued) when they do not fit.
@@ -701,10 +712,10 @@ ws_status use_static_workspace(ws_cache* c, AttnPlan& pv, AttnPlan& pa) {
 // streams those pages for the video rows, and the audio kernel walks only
 // the pages the video call does not see.  The merge then folds, per (head,
 // row), the audio kernel's ranges and the ranges the video kernel wrote.
-// Fills the fused plans and *rider_ranges (the most video ranges of a head);
-// false (plans untouched) when the step does not qualify.
+// Fills the fused plans; false (plans untouched) when the step does not
+// qualify.
 bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* audio, AttnPlan& pv, AttnPlan& pa,
-                 int* rider_ranges) {
+                 int64_t room) {
   if (c->opt_separate_audio || audio->desc.mode != WS_QUERY_PREPARED) return false;
   if (pv.a.n_classes != 1 || pv.a.cls[0].n_pages == 0) return false;
   const ws::AttnClass& cl = pv.a.cls[0];
@@ -743,28 +754,36 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
     rmax = std::max(rmax, static_cast<int>(ws::video_group_of(part, h0 + cl.n_pages - 1) -
                                            ws::video_group_of(part, h0) + 1));
   }
-  // The rows' own pages go to the video kernel when its last query tile
-  // leaves at least kRiderMinIdleWaves waves without rows (they attend the
-  // pages while the others start their first segment) and the page list
-  // stays inline; otherwise to the audio kernel.
+  // The rows' own pages go to the video kernel (its last wave in the last
+  // query tile attends them) when the page list stays inline and that wave has
+  // no rows or little to do; otherwise, or when audio key ranges are forced,
+  // to the audio kernel.  Each of a head's ranges takes its part of them as a
+  // key range of its own, as far as the workspace holds them (`room` partial
+  // rows).
+  const int64_t row_set = static_cast<int64_t>(H) * n_rq;
+  const bool inline_list = pv.a.pages == nullptr && pv.a.n_pages + n_extra <= ws::AttnArgs::kInlinePages;
+  int rx_ranges = 0, splits = 0, pps = 0;
   const int last_rows = rq_row0 + n_rq - (cl.n_qtiles - 1) * ws::kVideoQTile;
-  const int idle_waves = ws::kVideoWaves - (last_rows + 31) / 32;
-  const bool in_video = n_extra > 0 && c->opt_audio_splits == 0 && pv.a.pages == nullptr &&
-                        idle_waves >= kRiderMinIdleWaves &&
-                        pv.a.n_pages + n_extra <= ws::AttnArgs::kInlinePages;
-  const int rx_waves = in_video ? std::min(idle_waves, n_extra) : 0;
-  int splits = 0, pps = 0;
-  if (n_extra > 0 && !in_video) {
+  const bool idle_wave = last_rows <= (ws::kVideoWaves - 1) * ws::video_wave_rows(last_rows);
+  // A wave with rows of its own attends the pages after its segment, 16 rows at
+  // a time: worth it for one pass over a few pages (about 1 us each) against
+  // the audio kernel's launch (6 us).
+  const bool few = n_rq <= ws::kAudioQTile && n_extra <= kRiderPagesPerBusyWave * rmax;
+  if (n_extra > 0 && inline_list && c->opt_audio_splits == 0 && (idle_wave || few))
+    rx_ranges = static_cast<int>(std::min<int64_t>(std::min(rmax, n_extra), std::max<int64_t>(room / row_set - rmax, 0)));
+  if (n_extra > 0 && rx_ranges == 0) {
     // few pages (latency-bound): as many ranges as give each wave of the
     // audio kernel at most kRiderPagesPerRange / 4 pages
     splits = c->opt_audio_splits > 0 ? c->opt_audio_splits
+             : room < (rmax + n_extra) * row_set ? 1
                                      : (n_extra + kRiderPagesPerRange - 1) / kRiderPagesPerRange;
     splits = std::max(1, std::min(splits, n_extra));
     pps = (n_extra + splits - 1) / splits;
     splits = (n_extra + pps - 1) / pps;
   }
-  const int ranges = splits + rmax + rx_waves;
-  if (static_cast<int64_t>(ranges) * H * n_rq > c->part_rows) return false;
+  const bool in_video = rx_ranges > 0;
+  const int ranges = splits + rmax + rx_ranges;
+  if (ranges * row_set > c->part_rows) return false;
 
   ws::AttnArgs& aa = pa.a;
   for (int32_t i = 0; i < n_extra; ++i)
@@ -781,12 +800,12 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   pa.cb.r_pages = cl.n_pages;
   pa.cb.r_groups = cl.n_groups;
   pa.cb.seg_cost = pv.a.seg_cost;
-  pa.cb.r_extra = rx_waves;
+  pa.cb.r_extra = rx_ranges;
   ws::AttnArgs& av = pv.a;
   if (in_video) {
     av.rx_page0 = pv.a.n_pages;
     av.rx_pages = n_extra;
-    av.rx_waves = rx_waves;
+    av.rx_ranges = rx_ranges;
     for (int32_t i = 0; i < n_extra; ++i)
       av.inline_pages[av.rx_page0 + i] = make_int2(c->scratch_list[static_cast<size_t>(i)].page,
                                                    c->scratch_list[static_cast<size_t>(i)].n_valid);
@@ -796,7 +815,6 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   av.rq_head_stride = audio->q_head_stride;
   av.n_rq = n_rq;
   av.rq_row0 = rq_row0;
-  *rider_ranges = rmax;
   return true;
 }
 
@@ -828,8 +846,8 @@ ws_status step_attention_impl(ws_cache* c, const ws_attn_call* video, const ws_a
     if (ws_status st = plan_video(); st != WS_OK) return st;
     if (c->arena_wraps != wraps + 1) return fail(WS_ERR_SHAPE, "page-list arena too small for one step");
   }
-  int rider_ranges = 0;
-  const bool riders = plan_riders(c, video, audio, pv, pa, &rider_ranges);
+  const int64_t room = std::min(c->part_rows, static_workspace ? static_audio_rows(pv) : c->part_rows);
+  const bool riders = plan_riders(c, video, audio, pv, pa, room);
   if (static_workspace)
     if (ws_status st = use_static_workspace(c, pv, pa); st != WS_OK) return st;
   if (riders) {  // the video kernel's ranges of the audio rows follow the audio kernel's

@@ -88,6 +88,69 @@ __host__ __device__ inline int64_t video_group_lo(const VideoPartition& p, int64
   return static_cast<int64_t>(h * pages + (o > cost ? o - cost : 0u));
 }
 
+// Division of x < 2^31 by a fixed d >= 1 as a multiplication: with
+// l = ceil(log2 d) and mul = ceil(2^(31 + l) / d) < 2^32, mul d exceeds
+// 2^(31 + l) by less than d <= 2^l, so x times that excess stays below
+// 2^(31 + l) and floor(x mul / 2^(31 + l)) = floor(x / d).  d = 1 is mul = 0.
+struct FastDiv {
+  uint32_t mul, shift;
+};
+inline FastDiv make_fast_div(uint32_t d) {
+  if (d <= 1) return FastDiv{0, 0};
+  uint32_t l = 0;
+  while ((uint64_t(1) << l) < d) ++l;
+  return FastDiv{static_cast<uint32_t>(((uint64_t(1) << (31 + l)) + d - 1) / d), l - 1};
+}
+__host__ __device__ inline uint32_t fast_div(uint32_t x, FastDiv f) {
+  const uint32_t q = static_cast<uint32_t>((static_cast<uint64_t>(x) * f.mul) >> 32) >> f.shift;
+  return f.mul ? q : x;
+}
+
+// The lookups of a VideoPartition in 32-bit multiplications (the attention
+// kernel's form; the same integers, for up to 46340 groups and units below
+// 2^31): floor(g len / G) = g floor(len / G) + floor(g (len mod G) / G).
+struct VideoPartition32 {
+  uint32_t pages, cost, len, groups;  // len = heads * (pages + cost)
+  uint32_t quot, rem;                 // len / groups, len % groups
+  uint32_t fits;                      // (len + 1) * (groups + 1) < 2^31
+  FastDiv by_pages, by_stride, by_groups, by_len;
+};
+inline VideoPartition32 make_part32(const VideoPartition& p) {
+  const int64_t len = p.heads * (p.pages + p.seg_cost);
+  VideoPartition32 q{};
+  q.pages = static_cast<uint32_t>(p.pages);
+  q.cost = static_cast<uint32_t>(p.seg_cost);
+  q.len = static_cast<uint32_t>(len);
+  q.groups = static_cast<uint32_t>(p.groups);
+  q.quot = q.len / q.groups;
+  q.rem = q.len % q.groups;
+  q.fits = (len + 1) * (p.groups + 1) < (int64_t(1) << 31);
+  q.by_pages = make_fast_div(q.pages);
+  q.by_stride = make_fast_div(q.pages + q.cost);
+  q.by_groups = make_fast_div(q.groups);
+  q.by_len = make_fast_div(q.len);
+  return q;
+}
+__host__ __device__ inline uint32_t part_first_place(const VideoPartition32& p, uint32_t g) {
+  return g * p.quot + fast_div(g * p.rem, p.by_groups);
+}
+__host__ __device__ inline uint32_t part_group_lo(const VideoPartition32& p, uint32_t g) {
+  const uint32_t v0 = part_first_place(p, g);
+  const uint32_t h = fast_div(v0, p.by_stride), o = v0 - h * (p.pages + p.cost);
+  return h * p.pages + (o > p.cost ? o - p.cost : 0u);
+}
+__host__ __device__ inline uint32_t part_group_of(const VideoPartition32& p, uint32_t x) {
+  const uint32_t h = fast_div(x, p.by_pages);
+  const uint32_t place = h * (p.pages + p.cost) + p.cost + (x - h * p.pages);
+  if (p.fits) return fast_div((place + 1) * p.groups + p.len - 1, p.by_len) - 1;
+  uint32_t lo = 0, hi = p.groups;  // the last group that starts at or before the place
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (part_first_place(p, mid) <= place) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
 struct RopeTables {
   const float2* tab[3];  // (cos, sin) per band: [max_pos[b]][pairs[b]]
   int32_t max_pos[3];
@@ -143,6 +206,8 @@ struct AppendArgs {
 // pages).  A call with queries of one unit is one class.
 struct AttnClass {
   int32_t q0, n_q, page0, n_pages, n_groups, n_qtiles, wg0, pad;
+  FastDiv by_qtiles;
+  VideoPartition32 part;
 };
 constexpr int kMaxClasses = 8;
 
@@ -197,12 +262,12 @@ struct AttnArgs {
   float* rpart_lse;
   // The rider rows' own pages (visible to them only), entries rx_page0 ..
   // rx_page0 + rx_pages - 1 of the inline page list (rx_pages = 0: none, or
-  // attended elsewhere): attended by the last rx_waves waves (which have no
-  // rows) of the last query tile's workgroup of the group holding each
-  // head's last page, one key range per wave after the head's ranges.
+  // attended elsewhere): attended by the last wave of the last query tile's
+  // workgroups, each of a head's first rx_ranges ranges its part of them, as
+  // one more key range each.
   int32_t rx_page0;
   int32_t rx_pages;
-  int32_t rx_waves;
+  int32_t rx_ranges;
   uint32_t* flags;
   int2 inline_pages[kInlinePages];
 };
@@ -222,7 +287,7 @@ struct CombineArgs {
   // gives (r_groups = 0: none).
   int32_t r_pages;
   int32_t r_groups;
-  int32_t r_extra;       // more ranges per head: the rows' own pages, from the video kernel's idle waves
+  int32_t r_extra;       // the first r_extra of those ranges come with one of the rows' own pages each
   int32_t n_q;
   int32_t num_heads;
   uint16_t* out;
@@ -232,7 +297,7 @@ struct CombineArgs {
 
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t stream, hipEvent_t start = nullptr,
                             hipEvent_t stop = nullptr);
-// Video path: 256-query tiles on 8 waves, 32x32x16 bf16 MFMA, LDS-staged
+// Video path: 256-query tiles on 4 waves, 16x16x32 bf16 MFMA, LDS-staged
 // pages; n_groups x n_qtiles workgroups, each with an even share of the
 // (head, page) units.
 hipError_t launch_unit_attention(const AttnArgs& a, hipStream_t stream, hipEvent_t start = nullptr,
@@ -297,7 +362,9 @@ inline int64_t video_group_count(int64_t heads, int64_t qtiles, int64_t pages, i
   }
   return best;
 }
-constexpr int kVideoWaves = kVideoQTile / 32;
+constexpr int kVideoWaves = 4;      // one per SIMD
+// Rows of a wave in a query tile of `rows` rows.
+constexpr int video_wave_rows(int rows) { return rows > kVideoQTile / 2 ? 64 : 32; }
 constexpr int kAudioQTile = 16;
 constexpr int kMaxAudioQ = 64;  // audio queries per call
 
