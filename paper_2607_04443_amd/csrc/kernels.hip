@@ -57,6 +57,59 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// max and sum over lanes l, l ^ 16 (kLane = 16) or l, l ^ 32 (v_permlane*_swap:
+// no LDS round trip)
+template <int kLane>
+__device__ __forceinline__ float pair_max(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int kLane>
+__device__ __forceinline__ float pair_sum(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// max over the wave (rotations within a row of 16, then the swaps)
+template <int kRor>
+__device__ __forceinline__ float ror_max(float v) {
+  const int u = __float_as_int(v);
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(u, u, 0x120 + kRor, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return pair_max<32>(pair_max<16>(ror_max<1>(ror_max<2>(ror_max<4>(ror_max<8>(v))))));
+}
+// sum over the 16 lanes of a row, in every lane
+template <int kRor>
+__device__ __forceinline__ float ror_add(float v) {
+  const int u = __float_as_int(v);
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(u, u, 0x120 + kRor, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_sum(float v) { return ror_add<1>(ror_add<2>(ror_add<4>(ror_add<8>(v)))); }
+// |x|^2 of the lane's words, in fp32 products and sums
+__device__ __forceinline__ float norm2_fma(u32x4 w) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float lo = bf16_lo(w[i]), hi = bf16_hi(w[i]);
+    s = fmaf(lo, lo, s);
+    s = fmaf(hi, hi, s);
+  }
+  return s;
+}
+// the same by the dot product instruction, added to acc
+__device__ __forceinline__ float norm2_words(u32x4 w, float acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t x = w[i];
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, x), acc, false);
+  }
+  return acc;
+}
+
 // (cos, sin) of rotary pair p (0..63) for a token at position pos (t, h, w).
 __device__ __forceinline__ float2 rope_cs(const RopeTables& r, int p, int pt, int ph, int pw) {
   const int p0 = r.pairs[0], p01 = r.pairs[0] + r.pairs[1];
@@ -101,6 +154,98 @@ __device__ __forceinline__ const_append_args append_args() {
   return (const_append_args)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// Four rotary pairs (4 c .. 4 c + 3) of a token: their (cos, sin).  A pair's
+// band is a select on its index, not a branch, so that the loads of several
+// tokens are in flight together.
+__device__ __forceinline__ void rope_pairs(const RopeTables& r, int c, const int (&pos)[3], float2 (&cs)[4]) {
+  const int p0 = r.pairs[0], p01 = p0 + r.pairs[1];
+  const float2* row[3] = {r.tab[0] + static_cast<int64_t>(pos[0]) * r.pairs[0],
+                          r.tab[1] + static_cast<int64_t>(pos[1]) * r.pairs[1] - p0,
+                          r.tab[2] + static_cast<int64_t>(pos[2]) * r.pairs[2] - p01};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int p = 4 * c + i;
+    cs[i] = (p < p0 ? row[0] : p < p01 ? row[1] : row[2])[p];
+  }
+}
+
+// RMS norm, gamma and rotation of one row's eight dims (x, dims 8 c .. of the 16
+// lanes of the row), times scale, rounded once to bf16.
+__device__ __forceinline__ u32x4 norm_rope_row(u32x4 x, const float (&g)[8], float eps, const float2 (&cs)[4],
+                                               float scale) {
+  const float inv = rsqrtf(row_sum(norm2_fma(x)) * (1.0f / kHeadDim) + eps);
+  u32x4 y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float y0 = bf16_lo(x[i]) * inv * g[2 * i];
+    const float y1 = bf16_hi(x[i]) * inv * g[2 * i + 1];
+    y[i] = pack_bf16((y0 * cs[i].x - y1 * cs[i].y) * scale, (y0 * cs[i].y + y1 * cs[i].x) * scale);
+  }
+  return y;
+}
+
+// A segment's rows of one tile as the append's arithmetic takes them: 16 lanes
+// per token row (lane c: dims 8 c ..), rows rr, rr + 16, rr + 32, rr + 48.
+struct AppendRows {
+  u32x4 x[4];
+  int pos[4][3];
+};
+__device__ __forceinline__ void load_rows(const_append_seg sg, int tok0, int head, bool norm_rope, int c, int rr,
+                                          AppendRows& r) {
+  const uint16_t* src = sg->k;
+  const int64_t tok_stride = sg->tok_stride;
+  const int n_tokens = sg->n_tokens;
+  const int32_t* positions = sg->positions;
+  src += head * sg->head_stride + 8 * c;
+  if (norm_rope) {
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+      const int tok = min(tok0 + pass * 16 + rr, n_tokens - 1);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) r.pos[pass][b] = positions[3 * tok + b];
+    }
+  }
+#pragma unroll
+  for (int pass = 0; pass < 4; ++pass) {
+    const int tok = tok0 + pass * 16 + rr;
+    r.x[pass] = tok < n_tokens ? *reinterpret_cast<const u32x4*>(src + tok * tok_stride) : (u32x4){0u, 0u, 0u, 0u};
+  }
+}
+__device__ __forceinline__ void load_gamma(const_append_seg sg, int c, float (&g)[8]) {
+  const float* gamma = sg->gamma;
+  const float4 g0 = *reinterpret_cast<const float4*>(gamma + 8 * c);
+  const float4 g1 = *reinterpret_cast<const float4*>(gamma + 8 * c + 4);
+  g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w;
+  g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
+}
+// store(pass, slot, words) for the tile's 64 rows: normed, rotated and scaled
+// (two rows' table entries in flight at a time, which keeps the registers to
+// six blocks per CU), or scaled only.
+template <class F>
+__device__ __forceinline__ void rotate_rows(const RopeTables& rope, uint32_t* flags, const_append_seg sg, int tok0,
+                                            float scale, int c, int rr, AppendRows& r, F&& store) {
+  float g[8];
+  load_gamma(sg, c, g);
+  const float eps = sg->eps;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    float2 cs[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      // (a row past the end holds the last token's positions)
+      int (&p)[3] = r.pos[2 * half + k];
+      int q[3];
+      clamp_pos(rope, p[0], p[1], p[2], flags, q[0], q[1], q[2]);
+      rope_pairs(rope, c, q, cs[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int pass = 2 * half + k, slot = pass * 16 + rr;
+      store(pass, slot, norm_rope_row(r.x[pass], g, eps, cs[k], scale));
+    }
+  }
+}
+
 // Query preparation, one block of an append launch: tokens 64 chunk ..
 // 64 chunk + 63 of query set si, one head, 16 threads per token row as in
 // the key path below.  Q'' = RoPE(RMSNorm(Q) * gamma, positions) * scale *
@@ -109,78 +254,29 @@ __device__ __forceinline__ const_append_args append_args() {
 // instead of once per workgroup that reads the queries.
 __device__ __forceinline__ void prepare_queries(const RopeTables& rope, uint32_t* flags, const_append_seg sg,
                                                 int chunk, int head) {
-  const uint16_t* src = sg->k;
-  const int64_t tok_stride = sg->tok_stride, head_stride = sg->head_stride;
   const int n_tokens = sg->n_tokens;
   const bool norm_rope = (sg->mode & 1) != 0;
   const float scale = sg->scale_log2;
-  uint16_t* dst = sg->q_out;
-  const int64_t out_tok_stride = sg->out_tok_stride, out_head_stride = sg->out_head_stride;
   const int t = threadIdx.x, c = t & 15, rr = t >> 4;
   const int tok0 = chunk * kPageTokens;
-  float g[8];
-  float eps = 0.f;
-  const int32_t* positions = nullptr;
+  AppendRows r;
+  load_rows(sg, tok0, head, norm_rope, c, rr, r);
+  uint16_t* const dst = sg->q_out + head * sg->out_head_stride + 8 * c;
+  const int64_t out_tok_stride = sg->out_tok_stride;
+  auto put = [&](int, int slot, u32x4 y) {
+    const int tok = tok0 + slot;
+    if (tok < n_tokens) *reinterpret_cast<u32x4*>(dst + tok * out_tok_stride) = y;
+  };
   if (norm_rope) {
-    const float* gamma = sg->gamma;
-    eps = sg->eps;
-    positions = sg->positions;
-    const float4 g0 = *reinterpret_cast<const float4*>(gamma + 8 * c);
-    const float4 g1 = *reinterpret_cast<const float4*>(gamma + 8 * c + 4);
-    g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w;
-    g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
-  }
-  u32x4 qx[4];
-  int tpos[4][3];
+    rotate_rows(rope, flags, sg, tok0, scale, c, rr, r, put);
+  } else {
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int tok = tok0 + pass * 16 + rr;
-    const bool valid = tok < n_tokens;
-    qx[pass] = valid ? *reinterpret_cast<const u32x4*>(src + tok * tok_stride + head * head_stride + 8 * c)
-                     : (u32x4){0u, 0u, 0u, 0u};
-    if (norm_rope && valid) {
-      tpos[pass][0] = positions[3 * tok + 0];
-      tpos[pass][1] = positions[3 * tok + 1];
-      tpos[pass][2] = positions[3 * tok + 2];
-    } else {
-      tpos[pass][0] = tpos[pass][1] = tpos[pass][2] = 0;
+    for (int pass = 0; pass < 4; ++pass) {
+      u32x4 y;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = pack_bf16(bf16_lo(r.x[pass][i]) * scale, bf16_hi(r.x[pass][i]) * scale);
+      put(pass, pass * 16 + rr, y);
     }
-  }
-#pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int tok = tok0 + pass * 16 + rr;
-    const bool valid = tok < n_tokens;
-    const u32x4 x = qx[pass];
-    u32x4 y;
-    if (norm_rope) {
-      float f[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        f[2 * i] = bf16_lo(x[i]);
-        f[2 * i + 1] = bf16_hi(x[i]);
-      }
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
-      ss += __shfl_xor(ss, 1);
-      ss += __shfl_xor(ss, 2);
-      ss += __shfl_xor(ss, 4);
-      ss += __shfl_xor(ss, 8);
-      const float inv = rsqrtf(ss * (1.0f / kHeadDim) + eps);
-      int pt = 0, ph = 0, pw = 0;
-      if (valid) clamp_pos(rope, tpos[pass][0], tpos[pass][1], tpos[pass][2], flags, pt, ph, pw);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float y0 = f[2 * i] * inv * g[2 * i];
-        const float y1 = f[2 * i + 1] * inv * g[2 * i + 1];
-        const float2 cs = rope_cs(rope, 4 * c + i, pt, ph, pw);
-        y[i] = pack_bf16((y0 * cs.x - y1 * cs.y) * scale, (y0 * cs.y + y1 * cs.x) * scale);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) y[i] = pack_bf16(bf16_lo(x[i]) * scale, bf16_hi(x[i]) * scale);
-    }
-    if (valid) *reinterpret_cast<u32x4*>(dst + tok * out_tok_stride + head * out_head_stride + 8 * c) = y;
   }
 }
 
@@ -189,9 +285,23 @@ __device__ __forceinline__ void prepare_queries(const RopeTables& rope, uint32_t
 // page or a 64-token chunk of a query set of one of up to
 // AppendArgs::kMaxSegs segments.  256 threads; vt and wave_norm2 are the
 // block's LDS, free again when the call returns.
+//
+// What bounds it: memory (a step of 924 queries and 1,180 new tokens over 40
+// heads moves 67 MB, 10 us at the rate of a large copy) and, before that, the
+// chain position -> table entry -> rotation of each row.  So a tile's loads are
+// all issued first, its table entries two rows ahead by a select instead of a
+// branch per band, and row sums are DPP rotations instead of LDS permutes.
+// V is transposed through LDS: rows of 128 d, the 16-byte chunk d / 8 of row r
+// at position (d / 8) ^ (r / 8), so that the 32-bit reads of a d pair over the
+// eight row groups hit different banks; two rows of V^T per thread halve the
+// LDS reads.  Measured (that step / its queries alone / 12 heads, 256
+// queries and 320 tokens): 17.1 / 7.8 / 7.1 us before, 14.4 / 7.6 / 5.2 us.
+// With registers for six blocks per CU it spills (25.7 us); grids of 3, 5 and 8
+// blocks per CU take 15.6, 16.1 and 15.9 us for the first, 4 takes 14.9 in the
+// same run.
 // ------------------------------------------------------------------------- //
-__device__ __forceinline__ void append_tile(const_append_args A, int item, int head,
-                                            uint16_t (*vt)[kHeadDim + 8], float* wave_norm2) {
+__device__ __forceinline__ void append_tile(const_append_args A, int item, int head, uint16_t (*vt)[kHeadDim],
+                                            float* wave_norm2) {
   const const_append_seg sg = A->seg + A->blk_seg[item];
   RopeTables rope;
 #pragma unroll
@@ -207,125 +317,68 @@ __device__ __forceinline__ void append_tile(const_append_args A, int item, int h
   }
   const int num_heads = A->num_heads;
   const int page = A->pages[item];
-  const uint16_t* src_k = sg->k;
-  const uint16_t* src_v = sg->v;
-  const int64_t tok_stride = sg->tok_stride, head_stride = sg->head_stride;
+  const int64_t tok_stride = sg->tok_stride;
   const int n_tokens = sg->n_tokens;
-  const int mode = sg->mode;
+  const bool norm_rope = sg->mode == 1;
   const int tok0 = A->blk_page[item] * kPageTokens;
   const int64_t tile = (static_cast<int64_t>(page) * num_heads + head) * kPageHeadElems;
   uint16_t* kdst = A->kpool + tile;
   uint16_t* vdst = A->vpool + tile;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, c = t & 15, rr = t >> 4;
 
-  // K: 16 threads per token row, 8 consecutive d each; 16 rows per pass.
-  // Alongside, the largest squared norm of the stored rows of the tile.
-  const int c = t & 15;
-  const int rr = t >> 4;
-  float norm2 = 0.f;
-  float g[8];
-  float eps = 0.f;
-  const int32_t* positions = nullptr;
-  if (mode == 1) {
-    const float* gamma = sg->gamma;
-    eps = sg->eps;
-    positions = sg->positions;
-    const float4 g0 = *reinterpret_cast<const float4*>(gamma + 8 * c);
-    const float4 g1 = *reinterpret_cast<const float4*>(gamma + 8 * c + 4);
-    g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w;
-    g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
-  }
-  // all loads of the tile are issued up front (K rows, V rows, positions)
-  u32x4 kx[4], vx[4];
-  int tpos[4][3];
+  // all loads of the tile are issued up front: positions, K rows, V rows
+  AppendRows r;
+  load_rows(sg, tok0, head, norm_rope, c, rr, r);
+  const uint16_t* const src_v = sg->v + head * sg->head_stride + 8 * c;
+  u32x4 vx[4];
 #pragma unroll
   for (int pass = 0; pass < 4; ++pass) {
     const int tok = tok0 + pass * 16 + rr;
-    kx[pass] = tok < n_tokens ? *reinterpret_cast<const u32x4*>(src_k + tok * tok_stride + head * head_stride + 8 * c)
-                              : (u32x4){0u, 0u, 0u, 0u};
-    if (mode == 1 && tok < n_tokens) {
-      tpos[pass][0] = positions[3 * tok + 0];
-      tpos[pass][1] = positions[3 * tok + 1];
-      tpos[pass][2] = positions[3 * tok + 2];
-    } else {
-      tpos[pass][0] = tpos[pass][1] = tpos[pass][2] = 0;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ch = t + 256 * i;
-    const int tok = tok0 + (ch >> 4);
-    vx[i] = tok < n_tokens ? *reinterpret_cast<const u32x4*>(src_v + tok * tok_stride + head * head_stride + 8 * (ch & 15))
-                           : (u32x4){0u, 0u, 0u, 0u};
-  }
-  // V rows go to LDS ([slot][d]) as soon as they arrive, which frees their
-  // registers before the key arithmetic
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ch = t + 256 * i;
-    *reinterpret_cast<u32x4*>(&vt[ch >> 4][8 * (ch & 15)]) = vx[i];
+    vx[pass] = tok < n_tokens ? *reinterpret_cast<const u32x4*>(src_v + tok * tok_stride) : (u32x4){0u, 0u, 0u, 0u};
   }
 
+  // K: alongside, the largest squared norm of the stored rows of the tile.  It
+  // only bounds scores (the softmax shift), so the dot product instruction does:
+  // exact products, fp32 sums; squares it may flush (|k| < 1.1e-19) could move
+  // a bound by less than 32 for the largest |q| whose square is finite.
+  float norm2 = 0.f;
+  auto put = [&](int, int slot, u32x4 y) {
+    *reinterpret_cast<u32x4*>(kdst + k_tile_index(slot, 8 * c)) = y;
+    norm2 = fmaxf(norm2, row_sum(norm2_words(y, 0.f)));
+  };
+  if (norm_rope) {
+    // empty slots hold zeros whatever gamma and eps are
+    rotate_rows(rope, flags, sg, tok0, 1.0f, c, rr, r, [&](int pass, int slot, u32x4 y) {
+      put(pass, slot, tok0 + slot < n_tokens ? y : (u32x4){0u, 0u, 0u, 0u});
+    });
+  } else {
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) put(pass, pass * 16 + rr, r.x[pass]);
+  }
+  norm2 = pair_max<32>(pair_max<16>(norm2));
+  if ((t & 63) == 0) wave_norm2[t >> 6] = norm2;
 #pragma unroll
   for (int pass = 0; pass < 4; ++pass) {
-    const int slot = pass * 16 + rr;
-    const int tok = tok0 + slot;
-    const bool valid = tok < n_tokens;
-    const u32x4 x = kx[pass];
-    u32x4 y = x;
-    if (mode == 1) {
-      float f[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        f[2 * i] = bf16_lo(x[i]);
-        f[2 * i + 1] = bf16_hi(x[i]);
-      }
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
-      // the 16 threads of a row are 16 consecutive lanes
-      ss += __shfl_xor(ss, 1);
-      ss += __shfl_xor(ss, 2);
-      ss += __shfl_xor(ss, 4);
-      ss += __shfl_xor(ss, 8);
-      const float inv = rsqrtf(ss * (1.0f / kHeadDim) + eps);
-      int pt = 0, ph = 0, pw = 0;
-      if (valid) clamp_pos(rope, tpos[pass][0], tpos[pass][1], tpos[pass][2], flags, pt, ph, pw);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float y0 = f[2 * i] * inv * g[2 * i];
-        const float y1 = f[2 * i + 1] * inv * g[2 * i + 1];
-        const float2 cs = rope_cs(rope, 4 * c + i, pt, ph, pw);
-        y[i] = pack_bf16(y0 * cs.x - y1 * cs.y, y0 * cs.y + y1 * cs.x);
-      }
-      if (!valid) y = (u32x4){0u, 0u, 0u, 0u};
-    }
-    *reinterpret_cast<u32x4*>(kdst + k_tile_index(slot, 8 * c)) = y;
-    float ss = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ss += bf16_lo(y[i]) * bf16_lo(y[i]) + bf16_hi(y[i]) * bf16_hi(y[i]);
-    ss += __shfl_xor(ss, 1);
-    ss += __shfl_xor(ss, 2);
-    ss += __shfl_xor(ss, 4);
-    ss += __shfl_xor(ss, 8);
-    norm2 = fmaxf(norm2, ss);
+    const int row = pass * 16 + rr;
+    *reinterpret_cast<u32x4*>(&vt[row][8 * (c ^ (row >> 3))]) = vx[pass];
   }
-  norm2 = fmaxf(norm2, __shfl_xor(norm2, 16));
-  norm2 = fmaxf(norm2, __shfl_xor(norm2, 32));
-  if ((t & 63) == 0) wave_norm2[t >> 6] = norm2;
-
-  // V: staged [slot][d] in LDS above, written [d][slot].
   __syncthreads();
+  // thread: d pair d2 (two rows of V^T), slots 8 tc .. 8 tc + 7
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ch = t + 256 * i;
-    const int d = ch >> 3, tc = ch & 7;
-    u32x4 y;
+  for (int i = 0; i < 2; ++i) {
+    const int ch = t + 256 * i, tc = ch & 7, d = 2 * (ch >> 3);
+    uint32_t w[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      y[j] = static_cast<uint32_t>(vt[8 * tc + 2 * j][d]) |
-             (static_cast<uint32_t>(vt[8 * tc + 2 * j + 1][d]) << 16);
-    *reinterpret_cast<u32x4*>(vdst + v_tile_index(8 * tc, d)) = y;
+    for (int j = 0; j < 8; ++j)
+      w[j] = *reinterpret_cast<const uint32_t*>(&vt[8 * tc + j][8 * ((d >> 3) ^ tc) + (d & 7)]);
+    u32x4 lo, hi;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x05040100u);
+      hi[j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x07060302u);
+    }
+    *reinterpret_cast<u32x4*>(vdst + v_tile_index(8 * tc, d)) = lo;
+    *reinterpret_cast<u32x4*>(vdst + v_tile_index(8 * tc, d + 1)) = hi;
   }
   if (t == 0)
     A->knorm2[static_cast<int64_t>(page) * num_heads + head] =
@@ -338,7 +391,7 @@ __device__ __forceinline__ void append_tile(const_append_args A, int item, int h
 // blocks: their average life was about an eighth of the launch.)
 __global__ __launch_bounds__(256) void kv_append_kernel(const AppendArgs args) {
   (void)args;  // read in place, through append_args()
-  __shared__ __attribute__((aligned(16))) uint16_t vt[kPageTokens][kHeadDim + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t vt[kPageTokens][kHeadDim];
   __shared__ float wave_norm2[4];
   const const_append_args A = append_args();
   const int heads = A->num_heads;
@@ -471,41 +524,6 @@ __device__ __forceinline__ void mfma_drain() {
   sched_fence();
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   sched_fence();
-}
-
-// max and sum over lanes l, l ^ 16 (kLane = 16) or l, l ^ 32 (v_permlane*_swap:
-// no LDS round trip)
-template <int kLane>
-__device__ __forceinline__ float pair_max(float v) {
-  const uint32_t u = __float_as_uint(v);
-  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
-                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <int kLane>
-__device__ __forceinline__ float pair_sum(float v) {
-  const uint32_t u = __float_as_uint(v);
-  const auto r = kLane == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
-                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// max over the wave (rotations within a row of 16, then the swaps)
-template <int kRor>
-__device__ __forceinline__ float ror_max(float v) {
-  const int u = __float_as_int(v);
-  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(u, u, 0x120 + kRor, 0xf, 0xf, false)));
-}
-__device__ __forceinline__ float wave_max(float v) {
-  return pair_max<32>(pair_max<16>(ror_max<1>(ror_max<2>(ror_max<4>(ror_max<8>(v))))));
-}
-// |q|^2 of the lane's words, added to acc
-__device__ __forceinline__ float norm2_words(u32x4 w, float acc) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t x = w[i];
-    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, x), acc, false);
-  }
-  return acc;
 }
 
 // What one page's iteration addresses, computed a little at a time during the
