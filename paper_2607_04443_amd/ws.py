@@ -12,11 +12,12 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 # torch first: libws.so then binds to the HIP runtime torch has loaded, so
 # both share one runtime (loaded ahead of torch, libws.so pulls in the system
 # runtime, which found no device next to torch's ROCm build).
-import torch  # noqa: F401
+import torch
 
 from . import _build
 
@@ -345,20 +346,51 @@ def ws_last_error() -> str:
 # --------------------------------------------------------------------------- #
 # torch-facing convenience wrapper (marshalling only)
 # --------------------------------------------------------------------------- #
+# The native calls of a small step take 14 us of the host (three launches); the
+# marshalling around them took 26 us for 12 heads (field by field through
+# ctypes, torch's stream object, an import per tensor), more than the step's
+# kernels.  So each struct is packed in one call: 13 us.  Values that
+# struct.pack refuses and ctypes wraps or rounds go through ctypes, which also
+# reports what neither takes.
+_APPEND_ITEM = struct.Struct("@PPqq" "iiiiPPf4x")
+_QUERY_DESC = struct.Struct("@i4xPPff")
+_QUERY_ITEM = struct.Struct("@Pqqi4x" "i4xPPff" "Pqq")
+_ATTN_CALL = struct.Struct("@Pqqi4x" "i4xPPff" "12s4x" "Pqq")
+for _layout, _type in ((_APPEND_ITEM, ws_append_item), (_QUERY_DESC, ws_query_desc),
+                       (_QUERY_ITEM, ws_query_item), (_ATTN_CALL, ws_attn_call)):
+    assert _layout.size == ctypes.sizeof(_type), _type
+_BF16 = torch.bfloat16
+_current_device = torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream_handle(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
-def _check_tensor(name, t, dtype):
-    import torch
+def _rows(name, t):
+    """Strides of a bf16 [tokens, heads, 128] device tensor."""
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
-    if t.dtype != dtype:
-        raise ValueError(f"{name} must be {dtype}")
-    if dtype == torch.bfloat16 and (t.dim() != 3 or t.stride(2) != 1):
+    if t.dtype != _BF16:
+        raise ValueError(f"{name} must be {_BF16}")
+    strides = t.stride()
+    if len(strides) != 3 or strides[2] != 1:
         raise ValueError(f"{name} must be [tokens, heads, 128] with unit innermost stride")
+    return strides
+
+
+def _ptr(t):
+    return 0 if t is None else t.data_ptr()
+
+
+def _query_desc(mode, positions, gamma, eps, scale):
+    pos, gam = _ptr(positions), _ptr(gamma)
+    try:
+        return ws_query_desc.from_buffer_copy(_QUERY_DESC.pack(mode, pos, gam, eps, scale))
+    except (struct.error, OverflowError):
+        return ws_query_desc(mode, pos, gam, eps, scale)
 
 
 class Cache:
@@ -388,86 +420,77 @@ class Cache:
 
     @staticmethod
     def _item(unit, kind, k, v, mode=WS_APPEND_RAW, positions=None, gamma=None, eps=1e-6):
-        import torch
-        _check_tensor("k", k, torch.bfloat16)
-        _check_tensor("v", v, torch.bfloat16)
-        if k.stride() != v.stride() or k.shape != v.shape:
+        """The bytes of a ws_append_item."""
+        strides = _rows("k", k)
+        shape = k.shape
+        if _rows("v", v) != strides or shape != v.shape:
             raise ValueError("k and v must share shape and strides")
-        it = ws_append_item()
-        it.k, it.v = k.data_ptr(), v.data_ptr()
-        it.tok_stride, it.head_stride = k.stride(0), k.stride(1)
-        d = it.desc
-        d.unit, d.kind, d.n_tokens, d.mode = unit, kind, k.shape[0], mode
-        d.positions = positions.data_ptr() if positions is not None else None
-        d.gamma = gamma.data_ptr() if gamma is not None else None
-        d.eps = eps
-        return it
+        kp, vp, pos, gam = k.data_ptr(), v.data_ptr(), _ptr(positions), _ptr(gamma)
+        try:
+            return _APPEND_ITEM.pack(kp, vp, strides[0], strides[1], unit, kind, shape[0], mode, pos, gam, eps)
+        except (struct.error, OverflowError):
+            return bytes(ws_append_item(kp, vp, strides[0], strides[1],
+                                        ws_append_desc(unit, kind, shape[0], mode, pos, gam, eps)))
 
     def append(self, unit, kind, k, v, mode=WS_APPEND_RAW, positions=None, gamma=None, eps=1e-6,
                stream=None):
         it = self._item(unit, kind, k, v, mode, positions, gamma, eps)
-        ws_kv_append(self.handle, it.k, it.v, it.tok_stride, it.head_stride, it.desc,
-                     _stream_handle(stream))
+        ws_kv_append(self.handle, k.data_ptr(), v.data_ptr(), k.stride(0), k.stride(1),
+                     ws_append_desc.from_buffer_copy(it, ws_append_item.desc.offset), _stream_handle(stream))
 
     def append_many(self, items, stream=None):
         """items: dicts with the keyword arguments of append (stream aside)."""
-        ws_kv_append_many(self.handle, [self._item(**x) for x in items], _stream_handle(stream))
+        items = [self._item(**x) for x in items]
+        arr = (ws_append_item * len(items)).from_buffer_copy(b"".join(items))
+        _check(_lib.ws_kv_append_many(self.handle, len(items), arr, _stream_handle(stream)),
+               "ws_kv_append_many")
 
     @staticmethod
     def _query_item(q, q_out, mode=WS_APPEND_NORM_ROPE, positions=None, gamma=None, eps=1e-6,
                     scale=0.0):
-        import torch
-        _check_tensor("q", q, torch.bfloat16)
-        _check_tensor("q_out", q_out, torch.bfloat16)
-        if q.shape != q_out.shape:
+        """The bytes of a ws_query_item."""
+        st, out = _rows("q", q), _rows("q_out", q_out)
+        shape = q.shape
+        if shape != q_out.shape:
             raise ValueError("q and q_out must have the same shape")
-        it = ws_query_item()
-        it.q, it.tok_stride, it.head_stride, it.n_q = q.data_ptr(), q.stride(0), q.stride(1), q.shape[0]
-        d = it.desc
-        d.mode = mode
-        d.positions = positions.data_ptr() if positions is not None else None
-        d.gamma = gamma.data_ptr() if gamma is not None else None
-        d.eps, d.softmax_scale = eps, scale
-        it.q_out, it.out_tok_stride, it.out_head_stride = q_out.data_ptr(), q_out.stride(0), q_out.stride(1)
-        return it
+        qp, op, pos, gam = q.data_ptr(), q_out.data_ptr(), _ptr(positions), _ptr(gamma)
+        try:
+            return _QUERY_ITEM.pack(qp, st[0], st[1], shape[0], mode, pos, gam, eps, scale, op, out[0], out[1])
+        except (struct.error, OverflowError):
+            return bytes(ws_query_item(qp, st[0], st[1], shape[0], ws_query_desc(mode, pos, gam, eps, scale),
+                                       op, out[0], out[1]))
 
     def step_append(self, items=(), queries=(), stream=None):
         """One launch for a step's K/V appends (dicts with the keyword arguments
         of append) and query preparations (dicts with q, q_out, mode, positions,
         gamma, eps, scale); q_out then feeds the attention calls with mode
         WS_QUERY_PREPARED."""
-        ws_step_append(self.handle, [self._item(**x) for x in items],
-                       [self._query_item(**x) for x in queries], _stream_handle(stream))
+        items = [self._item(**x) for x in items]
+        queries = [self._query_item(**x) for x in queries]
+        arr = (ws_append_item * len(items)).from_buffer_copy(b"".join(items)) if items else None
+        qarr = (ws_query_item * len(queries)).from_buffer_copy(b"".join(queries)) if queries else None
+        _check(_lib.ws_step_append(self.handle, len(items), arr, len(queries), qarr, _stream_handle(stream)),
+               "ws_step_append")
 
     def _attn(self, fn, q, out, mask, mode, positions, gamma, eps, scale, stream):
-        import torch
-        _check_tensor("q", q, torch.bfloat16)
-        _check_tensor("out", out, torch.bfloat16)
-        qd = ws_query_desc()
-        qd.mode = mode
-        qd.positions = positions.data_ptr() if positions is not None else None
-        qd.gamma = gamma.data_ptr() if gamma is not None else None
-        qd.eps, qd.softmax_scale = eps, scale
-        fn(q.data_ptr(), q.stride(0), q.stride(1), q.shape[0], qd, self.handle, mask,
-           out.data_ptr(), out.stride(0), out.stride(1), _stream_handle(stream))
+        qs, os_ = _rows("q", q), _rows("out", out)
+        fn(q.data_ptr(), qs[0], qs[1], q.shape[0], _query_desc(mode, positions, gamma, eps, scale),
+           self.handle, mask, out.data_ptr(), os_[0], os_[1], _stream_handle(stream))
         return out
 
     @staticmethod
     def _call(q, out, mask, mode=WS_APPEND_NORM_ROPE, positions=None, gamma=None, eps=1e-6,
               scale=0.0):
-        import torch
-        _check_tensor("q", q, torch.bfloat16)
-        _check_tensor("out", out, torch.bfloat16)
-        c = ws_attn_call()
-        c.q, c.q_tok_stride, c.q_head_stride, c.n_q = q.data_ptr(), q.stride(0), q.stride(1), q.shape[0]
-        d = c.desc
-        d.mode = mode
-        d.positions = positions.data_ptr() if positions is not None else None
-        d.gamma = gamma.data_ptr() if gamma is not None else None
-        d.eps, d.softmax_scale = eps, scale
-        c.mask = mask
-        c.out, c.out_tok_stride, c.out_head_stride = out.data_ptr(), out.stride(0), out.stride(1)
-        return c
+        qs, os_ = _rows("q", q), _rows("out", out)
+        qp, op, pos, gam, n_q = q.data_ptr(), out.data_ptr(), _ptr(positions), _ptr(gamma), q.shape[0]
+        if type(mask) is ws_mask_spec:
+            try:
+                return ws_attn_call.from_buffer_copy(_ATTN_CALL.pack(
+                    qp, qs[0], qs[1], n_q, mode, pos, gam, eps, scale, bytes(mask), op, os_[0], os_[1]))
+            except (struct.error, OverflowError):
+                pass
+        return ws_attn_call(qp, qs[0], qs[1], n_q, ws_query_desc(mode, pos, gam, eps, scale), mask, op,
+                            os_[0], os_[1])
 
     def step_attention(self, video, audio, stream=None):
         """video, audio: dicts with the arguments of unit_attention /
@@ -489,21 +512,15 @@ class Cache:
     def unit_attention_groups(self, q, out, groups, mode=WS_APPEND_NORM_ROPE, positions=None,
                               gamma=None, eps=1e-6, scale=0.0, stream=None):
         """groups: (n_rows, ws_mask_spec) pairs; q's rows are the groups' rows in order."""
-        import torch
-        _check_tensor("q", q, torch.bfloat16)
-        _check_tensor("out", out, torch.bfloat16)
-        qd = ws_query_desc()
-        qd.mode = mode
-        qd.positions = positions.data_ptr() if positions is not None else None
-        qd.gamma = gamma.data_ptr() if gamma is not None else None
-        qd.eps, qd.softmax_scale = eps, scale
+        qs, os_ = _rows("q", q), _rows("out", out)
+        qd = _query_desc(mode, positions, gamma, eps, scale)
         gs = []
         for n, m in groups:
             g = ws_query_group()
             g.n_q, g.mask = n, m
             gs.append(g)
-        ws_unit_attention_groups(q.data_ptr(), q.stride(0), q.stride(1), gs, qd, self.handle,
-                                 out.data_ptr(), out.stride(0), out.stride(1), _stream_handle(stream))
+        ws_unit_attention_groups(q.data_ptr(), qs[0], qs[1], gs, qd, self.handle, out.data_ptr(),
+                                 os_[0], os_[1], _stream_handle(stream))
         return out
 
     def audio_attention(self, q, out, mask, mode=WS_APPEND_NORM_ROPE, positions=None,
@@ -562,7 +579,6 @@ class Block:
     layer (QKV projection, append, attention, output projection)."""
 
     def __init__(self, cache, w_qkv, w_out, max_rows):
-        import torch
         for name, w in (("w_qkv", w_qkv), ("w_out", w_out)):
             if not w.is_cuda or w.dtype != torch.bfloat16 or not w.is_contiguous():
                 raise ValueError(f"{name} must be a contiguous bf16 device tensor")
