@@ -333,9 +333,11 @@ typedef struct ws_attn_call {
  * Audio rows riding in the video kernel: when the audio call is
  * WS_QUERY_PREPARED, every page the video call sees is visible to the audio
  * call too, and the audio rows fit the spare rows of the video call's last
- * 256-query tile (n_audio <= 256 * ceil(n_video / 256) - n_video), the video
- * kernel also computes the audio rows over the video call's pages (the pages
- * are streamed once for both); the pages the audio call alone sees (the
+ * query tile (n_audio <= R * ceil(n_video / R) - n_video both for R = 256 and
+ * for the call's tiles of R = 256, 192 or 128 rows, which the library chooses
+ * from its heads, rows and pages), the video kernel also computes the audio
+ * rows over the video call's pages (the pages are streamed once for both); the
+ * pages the audio call alone sees (the
  * units' audio tokens) are walked by the last wave of the video kernel's last
  * query tile, or by the audio kernel when the page list does not travel in the
  * kernel arguments, audio key ranges are forced or the workspace is too small;

@@ -723,7 +723,9 @@ struct VideoState {
   bool in_reach;
   u32x4 ones;         // bf16 ones (an opaque value: not rematerialised in front of an MFMA)
 };
-constexpr int kRingAhead = 3;  // operand reads issued this many steps ahead
+// Operand reads are issued this many steps ahead.  (Six, through eight
+// registers, gives the narrower waves nothing: they are not latency-bound.)
+constexpr int kRingAhead = 3;
 
 // The queries live in accumulation registers (an MFMA reads its operands from
 // either bank), which leaves the vector registers to the softmax.
@@ -753,7 +755,7 @@ __device__ __forceinline__ void put_word(u32x4& p, int word, float lo, float hi)
 //   steps  8-15  P*V of p - 1, chunk 1      tile 0 of p (from step 10)
 //   steps 16-23  S tiles 2 and 3 of p       tile 1 of p
 //   steps 24-31  P*V of p, chunk 0          tile 2 of p (from step 26)
-// The subtiles' exponentials run in kQT / 2 streams, one exponential per
+// The subtiles' exponentials run in streams of two subtiles, one exponential per
 // stream and step (two in steps 10, 11, 26 and 27), each issued behind an MFMA
 // of its own (an exponential takes 8 of the 16 cycles of an MFMA, a pack 4)
 // and packed behind the next one, and each slot ends in a scheduling fence,
@@ -788,12 +790,16 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
   }
   f32x4 sa[4][kQT];
   u32x4 p0[kQT], p1n[kQT];
-  float e[kQT / 2][32];  // exponential x of a stream: tile x / 8, subtile (x / 4) % 2, register x % 4
+  // exponential x of a stream: tile x / 8, subtile (x / 4) % 2, register x % 4
+  // (the last stream of an odd kQT has one subtile)
+  constexpr int kStreams = (kQT + 1) / 2;
+  float e[kStreams][32];
 
   auto exp_x = [&](auto kc_, auto xc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc_)::value, x = decltype(xc)::value;
     constexpr int t = x >> 3, j = 2 * k + ((x >> 2) & 1), r = x & 3;
-    if constexpr (t == 3) {
+    if constexpr (j >= kQT) {
+    } else if constexpr (t == 3) {
       if constexpr (!kFirst) { e[k][x] = fast_exp2(st.s3[j][r]); pin_v(e[k][x]); }
     } else {
       e[k][x] = fast_exp2(sa[t][j][r]);
@@ -803,7 +809,8 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
   auto pack_x = [&](auto kc_, auto xc) __attribute__((always_inline)) {  // words of exponentials x, x + 1 (x even)
     constexpr int k = decltype(kc_)::value, x = decltype(xc)::value;
     constexpr int t = x >> 3, j = 2 * k + ((x >> 2) & 1), word = 2 * (t & 1) + ((x & 3) >> 1);
-    if constexpr (t == 3) {
+    if constexpr (j >= kQT) {
+    } else if constexpr (t == 3) {
       if constexpr (!kFirst) put_word(st.p1[j], word, e[k][x], e[k][x + 1]);
     } else if constexpr (t == 2) {
       put_word(p1n[j], word, e[k][x], e[k][x + 1]);
@@ -878,7 +885,7 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
     const bf16x8 a = st.ring[o & 3];
     static_for<kQT>([&](auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value, k = j >> 1;
-      constexpr bool even = (j & 1) == 0;
+      constexpr bool even = (j & 1) == 0, last = j == kQT - 1;
       // ---- the MFMA ----
       if constexpr (o < 8 || (o >= 16 && o < 24)) {
         constexpr int t = (o < 8 ? 0 : 2) + ((o & 7) >> 2);
@@ -912,7 +919,8 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
         else if constexpr (o == 26) exp_x(Const<k>{}, Const<16>{});
         else if constexpr (o == 27) exp_x(Const<k>{}, Const<18>{});
         else if constexpr (o >= 28) exp_x(Const<k>{}, Const<o - 8>{});
-      } else {
+      }
+      if constexpr (!even || last) {
         if constexpr (o < 8 && (o & 1)) pack_x(Const<k>{}, Const<24 + o - 1>{});
         else if constexpr (o == 10) exp_x(Const<k>{}, Const<1>{});
         else if constexpr (o == 11) { exp_x(Const<k>{}, Const<3>{}); pack_x(Const<k>{}, Const<0>{}); }
@@ -922,9 +930,11 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
         else if constexpr (o == 27) { exp_x(Const<k>{}, Const<19>{}); pack_x(Const<k>{}, Const<16>{}); }
         else if constexpr (o == 28) pack_x(Const<k>{}, Const<18>{});
         else if constexpr (o > 28 && (o & 1)) pack_x(Const<k>{}, Const<o - 9>{});
-        if constexpr (k == kQT / 2 - 1 && o < kDmaPerPage) issue_load<o>(s, c);
-        if constexpr (k == kQT / 2 - 1) next_ctx(oc);
-        if constexpr (k == kQT / 2 - 1 && (o == 14 || o == 30)) pin_v(st.ones);
+      }
+      if constexpr (last) {
+        if constexpr (o < kDmaPerPage) issue_load<o>(s, c);
+        next_ctx(oc);
+        if constexpr (o == 14 || o == 30) pin_v(st.ones);
       }
       sched_fence();
     });
@@ -1782,7 +1792,7 @@ __device__ __forceinline__ void rider_segments(const AttnArgs& a, const VideoWor
 
 // Rows that see nothing: output 0.
 __device__ __forceinline__ void video_empty(const AttnArgs& a, int head, int q_lo, int q_hi) {
-  const int n = min(kVideoQTile, q_hi - q_lo) * (kHeadDim / 8);
+  const int n = (q_hi - q_lo) * (kHeadDim / 8);
   for (int i = threadIdx.x; i < n; i += kVideoWaves * 64) {
     const int64_t q = q_lo + i / (kHeadDim / 8);
     *reinterpret_cast<u32x4*>(a.out + q * a.out_tok_stride + head * a.out_head_stride + 8 * (i % (kHeadDim / 8))) =
@@ -1817,10 +1827,10 @@ __device__ __forceinline__ void unit_attn(const AttnArgs& a) {
   const int group = static_cast<int>(fast_div(local, FastDiv{tab[ci].by_qtiles.mul, tab[ci].by_qtiles.shift}));
   const int qt = local - group * n_qtiles;
   const int q0 = tab[ci].q0, q_hi = q0 + tab[ci].n_q;
-  const int q_lo = q0 + qt * kVideoQTile;
+  const int tile_rows = tab[ci].tile_rows, q_lo = q0 + qt * tile_rows;
   // rider rows follow the video rows (a single class then)
-  const int row_end = min(q_lo + kVideoQTile, a.n_rq > 0 ? a.rq_row0 + a.n_rq : q_hi);
-  const bool wide = video_wave_rows(row_end - q_lo) == 64;
+  const int row_end = min(q_lo + tile_rows, a.n_rq > 0 ? a.rq_row0 + a.n_rq : q_hi);
+  const int wave_rows = video_wave_rows(tile_rows, row_end - q_lo);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
 
   VideoWork w;
@@ -1839,7 +1849,7 @@ __device__ __forceinline__ void unit_attn(const AttnArgs& a) {
   s.stage = 0;
   s.valid = 0;
   if (s.n_pages == 0) {  // nothing visible: one group per head
-    if (group < a.num_heads) video_empty(a, group, q_lo, q_hi);
+    if (group < a.num_heads) video_empty(a, group, q_lo, min(q_lo + tile_rows, q_hi));
     return;
   }
   w.part = part_of(tab[ci]);
@@ -1864,7 +1874,7 @@ __device__ __forceinline__ void unit_attn(const AttnArgs& a) {
     s.v_read = lds + kStageV + 128u * i16 + 16u * (g ^ ((i16 >> 1) & 7));
   }
   const bool rx = a.rx_pages > 0 && qt == n_qtiles - 1 && wave == kVideoWaves - 1;
-  if (q_lo + wave * (wide ? 64 : 32) >= row_end) {
+  if (q_lo + wave * wave_rows >= row_end) {
     stream_start(a, s);
     while (s.at < s.n) {
       const VideoSeg sg = video_seg(w, s, s.at);
@@ -1873,7 +1883,8 @@ __device__ __forceinline__ void unit_attn(const AttnArgs& a) {
     wait_dma_all();
     return;
   }
-  if (wide) video_wave<4, kPrepared>(a, w, s, wave);
+  if (wave_rows == 64) video_wave<4, kPrepared>(a, w, s, wave);
+  else if (wave_rows == 48) video_wave<3, kPrepared>(a, w, s, wave);
   else video_wave<2, kPrepared>(a, w, s, wave);
   if (rx) rider_segments(a, w, s);
 }

@@ -411,21 +411,10 @@ ws_status create_impl(const ws_cache_config* cfg, ws_cache** out) {
   return WS_OK;
 }
 
-// Number of workgroup groups of the video kernel (a group is one workgroup
-// per query tile; together the groups share the (head, page) units evenly;
-// one round of groups fits the CUs when groups * n_qtiles <= CUs): the cost
-// model of ws::video_group_count.  A forced split count s gives H * s
-// groups: every head in s equal key ranges.
 // Partition cost of starting a head's segment inside a workgroup's share, in
 // pages: the segment switch (epilogue stores, query load, key-norm bound,
 // pipeline refill) takes about as long as six pages of the main loop.
 constexpr int kVideoSegCostPages = 6;
-
-int choose_video_groups(const ws_cache* c, int n_heads, int n_qtiles, int n_pages, int n_cus) {
-  if (n_pages == 0) return n_heads;
-  if (c->opt_video_splits > 0) return n_heads * c->opt_video_splits;
-  return static_cast<int>(ws::video_group_count(n_heads, n_qtiles, n_pages, n_cus));
-}
 
 int choose_audio_splits(const ws_cache* c, int n_items, int n_pages) {
   if (c->opt_audio_splits > 0) return c->opt_audio_splits;
@@ -561,6 +550,7 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
     // latter).
     int64_t work = 0;
     for (int k = 0; k < n_cls; ++k) {
+      a.cls[k].tile_rows = ws::kVideoQTile;
       a.cls[k].n_qtiles = (a.cls[k].n_q + ws::kVideoQTile - 1) / ws::kVideoQTile;
       work += static_cast<int64_t>(a.cls[k].n_qtiles) * a.cls[k].n_pages;
     }
@@ -575,7 +565,14 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
       const int cus = c->opt_class_cus == 1 || n_cls == 1 || work == 0
                           ? c->num_cus
                           : static_cast<int>(std::max<int64_t>(cl.n_qtiles, c->num_cus * w / work));
-      cl.n_groups = choose_video_groups(c, H, cl.n_qtiles, cl.n_pages, cus);
+      if (c->opt_video_splits > 0 && cl.n_pages > 0) {  // (forced splits keep the full tile)
+        cl.n_groups = H * c->opt_video_splits;
+      } else {
+        const ws::VideoTiling t = ws::video_tiling(H, cl.n_q, cl.n_pages, cus);
+        cl.tile_rows = t.rows;
+        cl.n_qtiles = (cl.n_q + t.rows - 1) / t.rows;
+        cl.n_groups = static_cast<int32_t>(t.groups);
+      }
       cl.wg0 = wg;
       cl.by_qtiles = ws::make_fast_div(cl.n_qtiles);
       cl.part = ws::make_part32(ws::VideoPartition{H, std::max(cl.n_pages, 1), seg_cost, cl.n_groups});
@@ -589,7 +586,7 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
         merge = true;
         max_ranges = std::max<int64_t>(max_ranges, c->opt_video_splits > 0
                                                        ? c->opt_video_splits
-                                                       : std::max(2, (cl.n_groups + H - 1) / H + 1));
+                                                       : ws::video_max_ranges(H, cl.n_groups));
       }
     }
     if (cap < max_ranges) return fail(WS_ERR_SHAPE, "split-KV workspace too small");
@@ -722,7 +719,8 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   const int H = c->cfg.num_heads;
   const int n_rq = audio->n_q;
   const int rq_row0 = video->n_q;
-  if (rq_row0 + n_rq > cl.n_qtiles * ws::kVideoQTile) return false;
+  const int full = (rq_row0 + ws::kVideoQTile - 1) / ws::kVideoQTile * ws::kVideoQTile;
+  if (rq_row0 + n_rq > std::min(full, cl.n_qtiles * cl.tile_rows)) return false;
   // the audio call's pages that the video call does not see; every video
   // page must be among the audio call's
   c->pt.visible_pages(ws::MaskSpec{video->mask.q_unit, video->mask.min_visible_unit, video->mask.kind_mask},
@@ -763,8 +761,8 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   const int64_t row_set = static_cast<int64_t>(H) * n_rq;
   const bool inline_list = pv.a.pages == nullptr && pv.a.n_pages + n_extra <= ws::AttnArgs::kInlinePages;
   int rx_ranges = 0, splits = 0, pps = 0;
-  const int last_rows = rq_row0 + n_rq - (cl.n_qtiles - 1) * ws::kVideoQTile;
-  const bool idle_wave = last_rows <= (ws::kVideoWaves - 1) * ws::video_wave_rows(last_rows);
+  const int last_rows = rq_row0 + n_rq - (cl.n_qtiles - 1) * cl.tile_rows;
+  const bool idle_wave = last_rows <= (ws::kVideoWaves - 1) * ws::video_wave_rows(cl.tile_rows, last_rows);
   // A wave with rows of its own attends the pages after its segment, 16 rows at
   // a time: worth it for one pass over a few pages (about 1 us each) against
   // the audio kernel's launch (6 us).

@@ -205,7 +205,7 @@ struct AppendArgs {
 // workgroups starting at workgroup wg0 (VideoPartition over this class's
 // pages).  A call with queries of one unit is one class.
 struct AttnClass {
-  int32_t q0, n_q, page0, n_pages, n_groups, n_qtiles, wg0, pad;
+  int32_t q0, n_q, page0, n_pages, n_groups, n_qtiles, wg0, tile_rows;
   FastDiv by_qtiles;
   VideoPartition32 part;
 };
@@ -323,7 +323,7 @@ constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 // device (hipGetSymbolAddress) and kept.
 hipError_t static_scratch(void** ptr);
 
-constexpr int kVideoQTile = 256;
+constexpr int kVideoQTile = 256;    // rows of a video query tile, at most
 constexpr int kMaxVideoSplits = 8;  // key-range splits of the video kernel
 
 // Whether a partition into `groups` shares splits some head over more than
@@ -349,23 +349,94 @@ inline int64_t video_group_count(int64_t heads, int64_t qtiles, int64_t pages, i
   if (4 * one_round < g_max) g_max = 4 * one_round;
   int64_t best = heads < g_max ? heads : g_max;
   double best_cost = -1.0;
-  for (int64_t g = 1; g <= g_max; ++g) {
-    const double rounds = static_cast<double>((g + one_round - 1) / one_round);
-    const bool aligned = g % heads == 0 || heads % g == 0;
-    const double segs = static_cast<double>(aligned ? (g > heads ? g : heads) : g + heads - 1) / g;
-    const double cost = rounds * (static_cast<double>(units) / g + kSegCostPages * segs) +
+  const int h = static_cast<int>(heads), top = static_cast<int>(g_max), round = static_cast<int>(one_round);
+  auto aligned = [&](int g) { return g % h == 0 || h % g == 0; };
+  auto consider = [&](int g, bool whole) {
+    const double segs = static_cast<double>(whole ? (g > h ? g : h) : g + h - 1) / g;
+    const double cost = (g + round - 1) / round * (static_cast<double>(units) / g + kSegCostPages * segs) +
                         (video_heads_split(heads, g) ? kMergeCostPages : 0.0);
-    if (best_cost < 0 || cost < best_cost - 1e-9) {
+    if (best_cost < 0 || cost < best_cost - 1e-9 || (cost < best_cost + 1e-9 && g < best)) {
       best = g;
       best_cost = cost;
     }
+  };
+  // Within a round the cost of the counts that cut heads falls with G, so the
+  // largest of a round, the divisors and the multiples of H are all that can
+  // be cheapest (a scan of every count takes 3 us of the host at 40 heads).
+  for (int g = 1; g < h && g <= top; ++g)
+    if (h % g == 0) consider(g, true);
+  for (int g = h; g <= top; g += h) consider(g, true);
+  for (int r = 1; (r - 1) * round < top; ++r) {
+    int g = r * round < top ? r * round : top;
+    while (g > (r - 1) * round && aligned(g)) --g;
+    if (g > (r - 1) * round) consider(g, false);
   }
   return best;
 }
 constexpr int kVideoWaves = 4;      // one per SIMD
-// Rows of a wave in a query tile of `rows` rows.
-constexpr int video_wave_rows(int rows) { return rows > kVideoQTile / 2 ? 64 : 32; }
+// Rows of a wave in a query tile of `rows` rows, of a class in tiles of tile_rows.
+constexpr int video_wave_rows(int tile_rows, int rows) { return rows > kVideoQTile / 2 ? tile_rows / kVideoWaves : 32; }
 constexpr int kAudioQTile = 16;
 constexpr int kMaxAudioQ = 64;  // audio queries per call
+
+// Rows per query tile of a video class: 256, 192 or 128 (waves of 64, 48 or 32
+// rows).  Wide tiles read a page from LDS once for more rows, so they win
+// where the workgroups fill the chip anyway; narrow ones where the row count
+// times the heads leaves CUs idle and splitting the heads' pages instead would
+// cost a merge and second segments.  The estimate, in us per workgroup:
+// pages at a time per page that falls with the tile and, as the chip's power
+// limit comes into play, rises with the workgroups that run at once; the launch
+// with its first segment, further segments and a split's merge.  Measured,
+// whole passes in us with tiles of 256 / 192 / 128 rows:
+//   12 heads,  252 rows,  13 pages      28.2 /  23.5 /  24.7   -> 192
+//   40 heads,  920 rows,  19 pages      49.5 /  47.3 /  51.2   -> 192
+//   17 heads,  333 rows,  38 pages      32.6 /  31.3 /  30.2   -> 128
+//   40 heads,  920 rows,  49 pages      69.0 /  62.0 /  71.2   -> 192 (rows normed in the kernel)
+//   40 heads,  920 rows, 139 pages       156 /   169 /   182   -> 256
+//   40 heads,  920 rows, 479 pages       499 /   524           -> 256
+// An audio call's few rows ride in the last tile where they fit: a tiling
+// without room for kAudioQTile rows counts a launch more, one that leaves no
+// idle wave there for those rows' own pages a little more.  A narrower tile
+// is taken only with no more key ranges per head than the widest's, so it
+// never needs more workspace.
+inline int video_max_ranges(int64_t heads, int64_t groups) {
+  return !video_heads_split(heads, groups) ? 1
+         : static_cast<int>((groups + heads - 1) / heads + 1 > 2 ? (groups + heads - 1) / heads + 1 : 2);
+}
+struct VideoTiling {
+  int rows;        // per query tile
+  int64_t groups;  // video_group_count of that tiling
+};
+inline double video_tiling_us(int64_t heads, int64_t n_q, int64_t pages, int64_t cus, const VideoTiling& t) {
+  const int64_t g = t.groups, qtiles = (n_q + t.rows - 1) / t.rows;
+  const int64_t one_round = cus / qtiles > 1 ? cus / qtiles : 1;
+  const int64_t rounds = (g + one_round - 1) / one_round;
+  const bool split = video_heads_split(heads, g);
+  const double segs = static_cast<double>(!split || g % heads == 0 ? (g > heads ? g : heads) : g + heads - 1) / g;
+  const double load = g * qtiles < cus ? static_cast<double>(g * qtiles) / cus : 1.0;
+  const int wave_rows = video_wave_rows(t.rows, static_cast<int>(n_q < t.rows ? n_q : t.rows));
+  const double page = (wave_rows == 64 ? 1.0 : wave_rows == 48 ? 0.83 : 0.6) * (0.49 + 0.96 * load);
+  const double first = wave_rows == 64 ? 14.5 : wave_rows == 48 ? 13.3 : 11.5;
+  const int last = static_cast<int>(n_q - (qtiles - 1) * t.rows) + kAudioQTile;
+  const double audio = last > t.rows ? 5.0 : last > (kVideoWaves - 1) * video_wave_rows(t.rows, last) ? 1.0 : 0.0;
+  return rounds * (static_cast<double>(heads * pages) / g * page + first + 5.0 * (segs - 1.0)) + (split ? 6.0 : 0.0) + audio;
+}
+inline VideoTiling video_tiling(int64_t heads, int64_t n_q, int64_t pages, int64_t cus) {
+  auto of = [&](int rows) { return VideoTiling{rows, video_group_count(heads, (n_q + rows - 1) / rows, pages, cus)}; };
+  VideoTiling best = of(kVideoQTile);
+  if (pages == 0 || n_q <= kVideoQTile / 2) return best;
+  const int ranges = video_max_ranges(heads, best.groups);
+  double best_us = video_tiling_us(heads, n_q, pages, cus, best);
+  for (int rows : {192, 128}) {
+    const VideoTiling t = of(rows);
+    if (video_max_ranges(heads, t.groups) > ranges) continue;
+    const double us = video_tiling_us(heads, n_q, pages, cus, t);
+    if (us < best_us) {
+      best = t;
+      best_us = us;
+    }
+  }
+  return best;
+}
 
 }  // namespace ws
