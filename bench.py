@@ -688,8 +688,8 @@ def pmc_summary(fetch_dir, write_dir, long_fetch=None, long_write=None):
               "## The v0.2 step (256 + 9 x 920 video keys)",
               "",
               "The step driver runs three steps (ws_step_append, then ws_step_attention with the audio "
-              "rows riding in the video kernel and the audio kernel over the 9 audio-token pages, 80 "
-              "workgroups), then the video and the audio attention three times each as separate calls "
+              "rows riding in the video kernel, which also attends the 9 audio-token pages), "
+              "then the video and the audio attention three times each as separate calls "
               "(the audio kernel over all 8572 keys, 480 workgroups).  unit_attn_kernel is the median "
               "over both kinds of launch.",
               ""]
