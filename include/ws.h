@@ -302,8 +302,8 @@ WS_API ws_status ws_unit_attention_groups(const void* q, int64_t q_tok_stride, i
 
 /* The same attention for the few audio latent queries of a unit (Sec. 3:
  * short, unsharded).  Memory-bound split-KV kernel: fp32 partials over key
- * ranges, merged by log-sum-exp.  Arguments as ws_unit_attention;
- * 1 <= n_q <= min(max_q_tokens, 64). */
+ * ranges, merged by log-sum-exp (few keys: one range, written directly).
+ * Arguments as ws_unit_attention; 1 <= n_q <= min(max_q_tokens, 64). */
 WS_API ws_status ws_audio_attention(const void* q, int64_t q_tok_stride, int64_t q_head_stride,
                              int32_t n_q, const ws_query_desc* qdesc, ws_cache* cache,
                              const ws_mask_spec* mask, void* out, int64_t out_tok_stride,

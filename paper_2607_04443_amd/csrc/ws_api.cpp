@@ -424,6 +424,13 @@ int choose_audio_splits(const ws_cache* c, int n_items, int n_pages) {
   return std::max(1, std::min({target, std::max(1, n_pages / 4), kMaxAudioSplits}));
 }
 
+// An audio call of at most this many pages takes a head's keys as one range,
+// written without a merge.  Measured at 4 to 24 heads and 4 to 20 queries, us
+// per call with ranges and merge / one range: 8 pages 11.6 / 9.1, 12 pages 11.6 /
+// 11.0, 16 pages 11.6 / 12.7 (a wave's pages are a chain: the line lies at three
+// per wave).
+constexpr int kAudioDirectPages = 12;
+
 // The logit scale times log2(e), folded into Q'' (0 selects 1/sqrt(128)).
 float scale_log2_of(float softmax_scale) {
   const double scale = softmax_scale > 0.f ? static_cast<double>(softmax_scale)
@@ -439,6 +446,7 @@ struct AttnPlan {
   ws::CombineArgs cb{};
   int splits = 1;  // audio: key ranges; video: workgroup groups
   int64_t part_rows = 0;  // (range, head, query) partial rows the kernel may write
+  int merged_splits = 1, merged_pps = 0;  // audio: the key ranges where a merge follows
 };
 
 ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_t q_head_stride,
@@ -537,9 +545,16 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
     const int pps = n_pages > 0 ? (n_pages + splits - 1) / splits : 0;
     splits = pps > 0 ? (n_pages + pps - 1) / pps : 1;  // no empty splits
     if (cap < splits) return fail(WS_ERR_SHAPE, "split-KV workspace too small");
-    a.n_splits = splits;
-    a.pages_per_split = pps;
     plan->part_rows = static_cast<int64_t>(splits) * H * n_q;
+    plan->merged_splits = splits;
+    plan->merged_pps = pps;
+    if (splits == 1 || (c->opt_audio_splits == 0 && n_pages <= kAudioDirectPages)) {
+      splits = 1;
+      a.audio_direct = 1;
+      merge = false;
+    }
+    a.n_splits = splits;
+    a.pages_per_split = a.audio_direct ? n_pages : pps;
   } else {
     // Per class: query tiles, and groups of workgroups sharing the class's
     // (head, page) units.  The classes share one round of the CUs in
@@ -602,7 +617,7 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
 
   plan->splits = splits;
   plan->merge = merge;
-  if (merge) {
+  if (merge || audio) {  // (audio: also what a step's rider rows take over)
     ws::CombineArgs& cb = plan->cb;
     cb = ws::CombineArgs{};
     cb.part_o = a.part_o;
@@ -790,6 +805,7 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   aa.pages = nullptr;
   aa.n_pages = n_extra;
   aa.n_splits = std::max(splits, 1);
+  aa.audio_direct = 0;  // the video kernel's ranges follow
   aa.pages_per_split = pps;
   pa.splits = splits;
   pa.part_rows = static_cast<int64_t>(ranges) * H * n_rq;
@@ -846,6 +862,12 @@ ws_status step_attention_impl(ws_cache* c, const ws_attn_call* video, const ws_a
   }
   const int64_t room = std::min(c->part_rows, static_workspace ? static_audio_rows(pv) : c->part_rows);
   const bool riders = plan_riders(c, video, audio, pv, pa, room);
+  if (!riders && pv.merge && pa.a.audio_direct) {  // a merge is launched anyway
+    pa.a.audio_direct = 0;
+    pa.a.n_splits = pa.splits = pa.cb.n_splits = pa.merged_splits;
+    pa.a.pages_per_split = pa.merged_pps;
+    pa.merge = true;
+  }
   if (static_workspace)
     if (ws_status st = use_static_workspace(c, pv, pa); st != WS_OK) return st;
   if (riders) {  // the video kernel's ranges of the audio rows follow the audio kernel's

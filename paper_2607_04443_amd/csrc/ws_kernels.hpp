@@ -237,6 +237,7 @@ struct AttnArgs {
   int32_t n_pages;
   int32_t n_splits;      // audio: key-range splits (the combine kernel merges them)
   int32_t pages_per_split;
+  int32_t audio_direct;  // audio: 1: one range per head, written to out in bf16 (no merge)
   int32_t n_groups;      // video: workgroup groups sharing the (head, page) units (all classes)
   int32_t seg_cost;      // video: partition cost of starting a head (VideoPartition)
   int32_t n_qtiles;      // audio: query tiles; video: all classes' query tiles
