@@ -412,8 +412,10 @@ ws_status create_impl(const ws_cache_config* cfg, ws_cache** out) {
 }
 
 // Partition cost of starting a head's segment inside a workgroup's share, in
-// pages: the segment switch (epilogue stores, query load, key-norm bound,
-// pipeline refill) takes about as long as six pages of the main loop.
+// pages: the segment switch (epilogue stores, query load, key-norm bound, the
+// first page's full wait).  Costs of 2, 3, 4, 5 and 8 pages instead of 6 take
+// 154.4, 153.7, 153.3, 153.5 and 155.7 us per step against 154.0 (40 heads, 920
+// rows, 139 pages), 493-498 against 496 at 479 pages: flat around here.
 constexpr int kVideoSegCostPages = 6;
 
 int choose_audio_splits(const ws_cache* c, int n_items, int n_pages) {
