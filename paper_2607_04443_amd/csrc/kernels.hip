@@ -1169,8 +1169,9 @@ __device__ __forceinline__ void prepare_rows(const AttnArgs& a, const RawQueries
         w[i] = pack_bf16((y0 * cs[j][i].x - y1 * cs[j][i].y) * a.scale_log2,
                          (y0 * cs[j][i].y + y1 * cs[j][i].x) * a.scale_log2);
       }
-      // (a row past the call's end is all zeros, and stays so)
-      st.q[j][s] = as_bf16x8(x.rider[j] ? x.raw[j][s] : w);
+      // riders come prepared; a row past the call's end stays all zeros (with
+      // eps = 0 its norm gives 0 * inf)
+      st.q[j][s] = as_bf16x8(x.ok[j] ? w : x.raw[j][s]);
     }
   }
 }
