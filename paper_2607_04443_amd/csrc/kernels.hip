@@ -100,7 +100,8 @@ __device__ __forceinline__ float norm2_fma(u32x4 w) {
   }
   return s;
 }
-// the same by the dot product instruction, added to acc
+// the same by the dot product instruction, added to acc: for bounds only (its
+// rounding and subnormals are the instruction's own)
 __device__ __forceinline__ float norm2_words(u32x4 w, float acc) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -1143,7 +1144,7 @@ __device__ __forceinline__ void prepare_rows(const AttnArgs& a, const RawQueries
     row[j][2] = a.rope.tab[2] + static_cast<int64_t>(pw) * a.rope.pairs[2] - p01;
     float ss = 0.f;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) ss = norm2_words(x.raw[j][s], ss);
+    for (int s = 0; s < 4; ++s) ss += norm2_fma(x.raw[j][s]);
     ss = pair_sum<32>(pair_sum<16>(ss));
     inv[j] = rsqrtf(ss * (1.0f / kHeadDim) + a.eps);
   }

@@ -41,3 +41,25 @@ def test_one_range_against_the_oracle_and_a_merge(ws, n_q, n_keys):
         assert (out == 0).all()
     finally:
         L.close()
+
+
+@pytest.mark.parametrize("n_keys", [50, 64 * 8, 64 * 12])
+def test_a_nan_row_is_the_same_with_one_range_and_with_a_merge(ws, n_keys):
+    """A query row of NaN gives a row of zeros however its keys are cut, and
+    leaves the other rows alone."""
+    rng = np.random.default_rng(760 + n_keys)
+    H = 3
+    q, k, v = (synth.normal_bf16(rng, (n, H, 128)) for n in (5, n_keys, n_keys))
+    q[2] = 0x7fc0
+    L = Loaded(ws, _workload(H, k, v), max_pages=n_keys // 64 + 8, max_q_tokens=64)
+    try:
+        pos = np.zeros((5, 3), np.int32)
+        rest = [0, 1, 3, 4]
+        ref = L.oracle(q[rest], pos[rest], 0, COND, mode=oracle.MODE_RAW)
+        for splits in (0, 1, 2):
+            L.cache.set_option(ws.WS_OPT_AUDIO_KV_SPLITS, splits)
+            got = L.run("audio", q, pos, 0, COND, mode=ws.WS_APPEND_RAW)
+            assert (got[2] == 0).all(), (splits, got[2])
+            assert_gates(got[rest], ref, label=f"{n_keys} keys, {splits} ranges")
+    finally:
+        L.close()

@@ -1,11 +1,13 @@
-"""Rows of a query tile past the end of their call (or of their query group)
-leave the rows before them alone: a ragged call whose queries are normed in
-the kernel, with eps = 0 (a row of zeros then has an infinite reciprocal
-norm), gives bit for bit what a call with the tile filled gives."""
+"""Queries normed in the video kernel.  Rows of a query tile past the end of
+their call (or of their query group) leave the rows before them alone: a
+ragged call with eps = 0 (a row of zeros then has an infinite reciprocal
+norm) gives bit for bit what a call with the tile filled gives.  And the mean
+square is an fp32 one: rows of 2^-64 (squares below fp32's normal range) are
+normed like any other."""
 import numpy as np
 import pytest
 
-from helpers import dev_f32, dev_i32, from_dev, to_dev
+from helpers import assert_gates, bf16_f64, dev_f32, dev_i32, from_dev, to_dev
 from paper_2607_04443_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +54,15 @@ def test_ragged_groups_equal_the_filled_tiles(ws, setup):
     got = from_dev(out)
     np.testing.assert_array_equal(got[:200], _unit(ws, setup, 256, 1)[:200])
     np.testing.assert_array_equal(got[200:], _unit(ws, setup, 128, 1)[:31])
+
+
+@pytest.mark.parametrize("e", [64, 66, 68, 70])
+def test_tiny_rows_are_normed(ws, setup, e):
+    import torch
+    cache, q, pos, gamma, mask = setup
+    cache.set_option(ws.WS_OPT_VIDEO_KV_SPLITS, 1)
+    out = torch.full_like(q, float("nan"))
+    cache.unit_attention(q * 2.0 ** -e, out, mask, ws.WS_APPEND_NORM_ROPE, pos, gamma, 0.0)
+    # scaling every row by a power of two leaves its RMS norm as it was, up to
+    # the bits that squares near 2^-2e lose (at least 9 of 24 remain, of 128 squares)
+    assert_gates(bf16_f64(from_dev(out)), bf16_f64(_unit(ws, setup, 256, 1)), label=f"rows of 2^-{e}")
