@@ -172,9 +172,8 @@ typedef enum ws_option {
                                   equal ranges (1..8) instead of the balanced share */
   WS_OPT_AUDIO_KV_SPLITS = 1,  /* key-range splits of the audio kernel (1..512) */
   /* Softmax shift of the video kernel: 0 = automatic (a query row's logit
-   * bound |q''| * max |k| when it is at most 40 in log2 units, above that the
-   * bound less 16 as long as the row's logits reach to within 80 of it, else
-   * a running maximum), 1 = always the running maximum. */
+   * bound |q''| * max |k| when it is at most 40 in log2 units, else a lazily
+   * raised running maximum), 1 = always the running maximum. */
   WS_OPT_VIDEO_RUNNING_MAX = 2,
   /* ws_unit_attention_groups: 0 = the query groups share one round of the
    * CUs in proportion to their work, 1 = every group is partitioned as if it
@@ -266,9 +265,10 @@ WS_API ws_status ws_kv_release(ws_cache* cache, int32_t unit, ws_kind kind);
  * those are merged by log-sum-exp in a second kernel.
  * The softmax shift of a query row is its logit bound |Q''_i| * max |K'_j|
  * (Cauchy-Schwarz over the pages of one key range) when that bound is at most
- * 40 in log2 units, above it the bound less 16 when the logits reach that far,
- * else a running maximum (WS_OPT_VIDEO_RUNNING_MAX forces the latter); all
- * give the same softmax. */
+ * 40 in log2 units, else a lazily raised running maximum
+ * (WS_OPT_VIDEO_RUNNING_MAX forces the latter); both give the same softmax.
+ * The choice is each row's own: a row's output does not depend on the other
+ * rows of the call. */
 WS_API ws_status ws_unit_attention(const void* q, int64_t q_tok_stride, int64_t q_head_stride,
                             int32_t n_q, const ws_query_desc* qdesc, ws_cache* cache,
                             const ws_mask_spec* mask, void* out, int64_t out_tok_stride,

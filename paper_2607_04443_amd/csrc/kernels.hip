@@ -7,7 +7,7 @@
 //  unit_attn       video queries: flash attention over the visible pages with
 //                  v_mfma_f32_16x16x32_bf16, K/V pages staged through a ring
 //                  of LDS stages, softmax in the exp2 domain under a shift
-//                  fixed in advance.
+//                  fixed in advance or a lazily raised running maximum.
 //  audio_attn      the few audio queries: memory-bound split-KV, one wave per
 //                  key range, v_mfma_f32_16x16x32_bf16 straight from registers.
 //  combine         log-sum-exp merge of split-KV partials.
@@ -40,11 +40,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr float kNegInf = -__builtin_inff();
 // Largest logit bound (log2 units) used as a fixed softmax shift.
 constexpr float kShiftBoundMax = 40.0f;
-// Above it the video kernel's fixed shift is the bound less this much (p stays
-// at most 2^16, which leaves O room for 2^15 keys of values up to 2^96) ...
-constexpr float kShiftBelowBound = 16.0f;
-// ... as long as the row's largest logit is at most this far below the shift.
-constexpr float kShiftReach = 80.0f;
+// Above it the video kernel's shift is a running maximum, raised when a logit
+// exceeds it by more than this (so p <= 2^8).
+constexpr float kRaiseAbove = 8.0f;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -512,6 +510,18 @@ __device__ __forceinline__ void mfma_o(f32x4& d, bf16x8 a, bf16x8 b) {
 __device__ __forceinline__ void mfma_o_first(f32x4& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(d) : "v"(a), "v"(b));
 }
+// An accumulator times a factor, in place: multiplied in plain code it would
+// move to vector registers, and the page loop around the branch with it.
+__device__ __forceinline__ void scale_acc(f32x4& d, float f) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float x = d[r], t;
+    asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                 : "+a"(x), "=&v"(t)
+                 : "v"(f));
+    d[r] = x;
+  }
+}
 // A value the compiler cannot carry over from an earlier computation: the
 // epilogue recomputes its addresses instead of keeping them live across the
 // page loop.
@@ -720,8 +730,10 @@ struct VideoState {
   f32x4 s3[kQT];      // S tile 3 of the previous page
   u32x4 p1[kQT];      // P words of its chunk 1 (tile 2's done)
   bf16x8 ring[4];     // operands in flight (slot = step % 4)
-  bool verify;        // some row's shift lies below its logit bound
-  bool in_reach;
+  // rows under a running maximum
+  bool any_lazy;      // some row of the wave is one
+  uint32_t raised;    // subtiles whose O and l wait to be scaled (bit j) ...
+  float scale[kQT];   // ... by this, row q
   u32x4 ones;         // bf16 ones (an opaque value: not rematerialised in front of an MFMA)
 };
 // Operand reads are issued this many steps ahead.  (Six, through eight
@@ -747,6 +759,26 @@ __device__ __forceinline__ void put_word(u32x4& p, int word, float lo, float hi)
   p[word] = w;
 }
 
+// O and l of the rows raised at the last check, scaled to their new m.  No MFMA
+// on them may be under way (the page loop: the last one was issued eight steps
+// before).
+template <int kQT>
+__device__ __forceinline__ void scale_raised(VideoState<kQT>& st) {
+  if (st.raised == 0) return;
+  sched_fence();
+#pragma unroll
+  for (int j = 0; j < kQT; ++j) {
+    if (st.raised >> j & 1) {
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) scale_acc(st.o[dt][j], st.scale[j]);
+      scale_acc(st.l[j], st.scale[j]);
+    }
+  }
+  st.raised = 0;
+  asm volatile("s_nop 7" ::: "memory");
+  sched_fence();
+}
+
 // One page, software-pipelined across pages so that the softmax work is
 // spread over the MFMA steps.  Iteration p (page p from the current stage,
 // V^T of page p - 1 from the one before it): 32 steps of one LDS operand read
@@ -766,9 +798,27 @@ __device__ __forceinline__ void put_word(u32x4& p, int word, float lo, float hi)
 // each wave waits for its loads of page p + 2, so every load has two pages to
 // land and the next page is complete a page before it is used.  One barrier
 // per page.
-// kFirst: a range's first page: no page p - 1; with st.verify set it also
-// checks that the shift is in reach of the rows' logits (st.in_reach).
-template <int kQT, bool kFirst>
+// kFirst: a range's first page: no page p - 1.
+//
+// Rows under a running maximum (st.any_lazy; after the first page the kLazy
+// form of the loop): the range's first 32 keys set a row's m to their maximum.
+// From then on the largest S (a difference to m) of every chunk is taken in the
+// steps that have no exponential (8 and 9, 24 and 25) and compared ahead of
+// the chunk's exponentials; where it exceeds kRaiseAbove, the row takes it as
+// its new m, and what O and l hold by then is scaled to it between the P*V of
+// the chunk before and the chunk's own (after step 23, and after step 7 of the
+// next page: their MFMAs are long done by then, and no P word is rounded
+// twice).  Every choice is the row's own, so a row's result does not depend on
+// the rows that share its wave, and a row under a fixed shift never exceeds it.
+// A raised row's largest weight is exactly 1 instead of rounded like the others,
+// which keeps the error of sharp attention down; a threshold of 4 gives more
+// such rows and more raises (9% slower), one of 16 fewer (0.3% more error).
+// Measured, 40 heads, 920 rows, 139 pages, us a step at query norm weights 1
+// (no such row), 3, 4 and 7: 157, 190, 207, 223; without raises the loop takes
+// 170.  (A shift fixed at 16 below the logit bound took 154 up to 4, but rounded
+// the largest weight, and out of its reach, from 5 on, the range ran unpipelined
+// under a running maximum: 344 to 455.)
+template <int kQT, bool kFirst, bool kLazy>
 __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) {
   const int n_valid = static_cast<int>(s.valid & 0xffu);
   const bool tail = n_valid < kPageTokens;
@@ -791,6 +841,7 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
   }
   f32x4 sa[4][kQT];
   u32x4 p0[kQT], p1n[kQT];
+  float cm[kQT], top;  // largest S of the lane's keys of a chunk, and of all subtiles
   // exponential x of a stream: tile x / 8, subtile (x / 4) % 2, register x % 4
   // (the last stream of an odd kQT has one subtile)
   constexpr int kStreams = (kQT + 1) / 2;
@@ -819,7 +870,44 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
       put_word(p0[j], word, e[k][x], e[k][x + 1]);
     }
   };
-  // a page tail's work on the chunk of tiles a and a + 1
+  // the largest S of chunk a (tiles a, a + 1) in this lane
+  auto take_max = [&](auto jc, auto ac) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value, a = decltype(ac)::value;
+    const f32x4 &x = sa[a][j], &y = sa[a + 1][j];
+    cm[j] = fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), x[2]), fmaxf(fmaxf(x[3], y[0]), y[1])), fmaxf(y[2], y[3]));
+    pin_v(cm[j]);
+  };
+  auto take_top = [&](auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    top = j == 0 ? cm[0] : fmaxf(top, cm[j]);
+    pin_v(top);
+  };
+  auto take_all = [&](auto ac) __attribute__((always_inline)) {
+    static_for<kQT>([&](auto jc) __attribute__((always_inline)) {
+      take_max(jc, ac);
+      take_top(jc);
+    });
+  };
+  // New maxima for the rows of a chunk that exceed theirs by too much.
+  auto raise = [&](auto ac) __attribute__((always_inline)) {
+    constexpr int a = decltype(ac)::value;
+    st.raised = 0;
+#pragma unroll
+    for (int j = 0; j < kQT; ++j) {
+      const float row = pair_max<32>(pair_max<16>(cm[j]));
+      if (__any(row > kRaiseAbove)) {
+        const float up = row > kRaiseAbove ? row : 0.f;  // (0: nothing of the row changes)
+        st.raised |= 1u << j;
+        st.scale[j] = fast_exp2(-up);
+        st.m[j] += up;
+        const float neg = -st.m[j];
+        st.s_init[j] = (f32x4){neg, neg, neg, neg};
+        sa[a][j] -= up;
+        sa[a + 1][j] -= up;
+      }
+    }
+  };
+  // a page tail's work on the chunk of tiles a and a + 1, and its maxima
   auto check_chunk = [&](auto ac) __attribute__((always_inline)) {
     constexpr int a = decltype(ac)::value;
     if (tail) {
@@ -834,19 +922,29 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
 #pragma unroll
           for (int j = 0; j < kQT; ++j)
             sa[t][j][r] = 32 * (t >> 1) + 4 * (t & 1) + r >= lim ? kNegInf : sa[t][j][r];
+      if constexpr (kLazy) take_all(ac);
     }
-    if constexpr (kFirst && a == 0) {
-      if (st.verify) {  // the S tiles hold logit - m
-        bool in_reach = true;
+    if constexpr (kFirst) {
+      if (st.any_lazy) {
+        take_all(ac);
+        if constexpr (a == 0) {
 #pragma unroll
-        for (int j = 0; j < kQT; ++j) {
-          const float mx = fmaxf(fmaxf(fmaxf(sa[0][j][0], sa[0][j][1]), fmaxf(sa[0][j][2], sa[0][j][3])),
-                                 fmaxf(fmaxf(sa[1][j][0], sa[1][j][1]), fmaxf(sa[1][j][2], sa[1][j][3])));
-          // (rows with the bound itself as their shift are in reach anyway)
-          in_reach = in_reach && pair_max<32>(pair_max<16>(mx)) >= -kShiftReach;
+          for (int j = 0; j < kQT; ++j) {
+            // (a page's first chunk has a valid key; clamped all the same)
+            const float row = fmaxf(pair_max<32>(pair_max<16>(cm[j])), -3.0e38f);
+            const float up = st.m[j] < 0.f ? row : 0.f;  // (m < 0: not set yet)
+            st.m[j] = st.m[j] < 0.f ? row : st.m[j];
+            const float neg = -st.m[j];
+            st.s_init[j] = (f32x4){neg, neg, neg, neg};
+            sa[0][j] -= up;
+            sa[1][j] -= up;
+          }
+        } else {
+          raise(ac);
         }
-        st.in_reach = __all(in_reach);
       }
+    } else if constexpr (kLazy) {
+      if (__any(top > kRaiseAbove)) raise(ac);
     }
     sched_fence();
   };
@@ -908,6 +1006,8 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
       }
       sched_fence();
       // ---- this slot's share of the rest ----
+      if constexpr (kLazy && (o == 8 || o == 24)) take_max(jc, Const<o == 8 ? 0 : 2>{});
+      if constexpr (kLazy && (o == 9 || o == 25)) take_top(jc);
       if constexpr (j == 1) {
         constexpr int n = o + kRingAhead;
         if constexpr (!(kFirst && n >= 8 && n < 16)) st.ring[n & 3] = oread(Const<n>{});
@@ -941,6 +1041,7 @@ __device__ __forceinline__ void video_iter(VideoState<kQT>& st, VideoStream& s) 
     });
     if constexpr (o == 9) check_chunk(Const<0>{});
     if constexpr (o == 25) check_chunk(Const<2>{});
+    if constexpr (kLazy && (o == 7 || o == 23)) scale_raised(st);
   });
 #pragma unroll
   for (int j = 0; j < kQT; ++j) {
@@ -964,6 +1065,7 @@ template <int kQT>
 __device__ __forceinline__ void video_flush(VideoState<kQT>& st, const VideoStream& s) {
   const uint32_t v1 = s.c.vp;
   mfma_drain();
+  scale_raised(st);
 #pragma unroll
   for (int j = 0; j < kQT; ++j)
 #pragma unroll
@@ -981,75 +1083,6 @@ __device__ __forceinline__ void video_flush(VideoState<kQT>& st, const VideoStre
 #pragma unroll
     for (int j = 0; j < kQT; ++j) mfma_o(st.o[dt][j], v[dt], as_bf16x8(st.p1[j]));
   mfma_drain();
-}
-
-// Advances the stream by a page, context and all (the pipelined iteration does
-// the same a little at a time).
-__device__ __forceinline__ void stream_advance(VideoStream& s) {
-  const uint32_t e = stream_peek(s, min(s.at + 4, s.n - 1));
-  s.valid = (s.valid >> 8) | ((e & 127u) << 24);
-  s.at += 1;
-  s.stage = ring_add(s.stage, 1);
-  set_load(s, e, ring_add(s.stage, 3), s.c);
-  set_reads(s, s.stage, s.c);
-  stream_reach(s);
-}
-
-// One page under a running maximum, subtile by subtile, not pipelined: for
-// rows whose shift cannot be fixed in advance (logits more than kShiftReach
-// below a bound above kShiftBoundMax, or the option that asks for it).
-// Starts from m = -inf with O and l zero.
-template <int kQT>
-__device__ __forceinline__ void video_page_running_max(VideoState<kQT>& st, const VideoStream& s, uint32_t stage,
-                                                       int n_valid) {
-  const uint32_t k0 = s.k_read + stage, v0 = s.v_read + stage;
-  const int lim = n_valid - 8 * (opaque(s.lane) >> 4);
-  static_for<kQT>([&](auto jc) __attribute__((always_inline)) {
-    constexpr int j = decltype(jc)::value;
-    f32x4 sa[4];
-    float mx = kNegInf;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      sa[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int n = 0; n < 4; ++n) mfma_s(sa[t], lds_read16((k0 ^ (64u * n)) + 4096u * t), st.q[j][n], sa[t]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sa[t][r] = 32 * (t >> 1) + 4 * (t & 1) + r >= lim ? kNegInf : sa[t][r];
-        mx = fmaxf(mx, sa[t][r]);
-      }
-    }
-    mx = pair_max<32>(pair_max<16>(mx));  // a page has a valid key: not -inf
-    const float m = fmaxf(st.m[j], mx);
-    if (__any(m != st.m[j])) {
-      const float alpha = fast_exp2(st.m[j] - m);
-      mfma_drain();
-      st.l[j] *= alpha;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) st.o[dt][j] *= alpha;
-    }
-    st.m[j] = m;
-    u32x4 p[2];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; r += 2)
-        p[t >> 1][2 * (t & 1) + (r >> 1)] = pack_bf16(fast_exp2(sa[t][r] - m), fast_exp2(sa[t][r + 1] - m));
-    pin_v(p[0]);
-    pin_v(p[1]);
-    pin_v(st.ones);
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      bf16x8 v[8];
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) v[dt] = lds_read16((v0 ^ (64u * c)) + 2048u * dt);
-      mfma_drain();
-      mfma_o(st.l[j], as_bf16x8(st.ones), as_bf16x8(p[c]));
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) mfma_o(st.o[dt][j], v[dt], as_bf16x8(p[c]));
-    }
-    mfma_drain();
-  });
 }
 
 // One segment of a video workgroup's stream: the query tile of rows
@@ -1195,11 +1228,8 @@ __device__ __forceinline__ void video_segment(const AttnArgs& a, const VideoSeg&
   // serves as the exp2 shift as it stands: p = exp2(s - B_q) <= 1, with no
   // running maximum and no rescale of O.  The row's largest p is at least
   // 2^(-2 B_q), so for B_q <= kShiftBoundMax every weight above 2^-46 of the
-  // row maximum stays a normal bf16/fp32 number.  Above that the shift is
-  // B_q - kShiftBelowBound: p <= 2^16, and the same holds as long as the row's
-  // largest logit is at most kShiftReach below the shift, which the range's
-  // first keys show in all but extreme cases; otherwise the range runs under a
-  // running maximum.
+  // row maximum stays a normal bf16/fp32 number.  Rows with a larger bound run
+  // under a running maximum (video_iter).
   float kn2 = 0.f;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -1208,63 +1238,36 @@ __device__ __forceinline__ void video_segment(const AttnArgs& a, const VideoSeg&
   }
   for (int k = max(s.at, 128) + s.lane; k < s.at + sg.n; k += 64)
     kn2 = fmaxf(kn2, a.knorm2[stream_entry(s, k) >> 7]);
-  kn2 = wave_max(kn2);
-  bool small = true;
+  kn2 = fminf(wave_max(kn2), 3.0e38f);  // (finite: a zero query's bound is 0)
+  bool lazy = false;
 #pragma unroll
   for (int j = 0; j < kQT; ++j) {
     float qn2 = 0.f;
 #pragma unroll
     for (int t = 0; t < 4; ++t) qn2 = norm2_words(__builtin_bit_cast(u32x4, st.q[j][t]), qn2);
     const float bound = sqrtf(pair_sum<32>(pair_sum<16>(qn2)) * kn2);
-    small = small && bound <= kShiftBoundMax;
-    st.m[j] = bound <= kShiftBoundMax ? bound : bound - kShiftBelowBound;
-  }
-  st.verify = !__all(small);
-  st.in_reach = true;
-  pin_queries(st);
-#pragma unroll
-  for (int j = 0; j < kQT; ++j) {
-    const float neg = -st.m[j];
+    const bool is = a.fixed_shift == 0 || bound > kShiftBoundMax;
+    lazy = lazy || is;
+    st.m[j] = is ? -1.f : bound;  // (-1: to be set by the first keys)
+    const float neg = is ? 0.f : -bound;
     st.s_init[j] = (f32x4){neg, neg, neg, neg};
   }
+  st.any_lazy = __any(lazy);
+  st.raised = 0;
+  pin_queries(st);
   st.ones = (u32x4){0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
   asm volatile("" : "+v"(st.ones));
 
   // ---- the segment's pages ----
   if (s.at == 0) wait_dma_all_but_last_page();
   const int end = s.at + sg.n;
-  const uint32_t stage0 = s.stage;
-  const int valid0 = static_cast<int>(s.valid & 0xffu);
-  video_iter<kQT, true>(st, s);
-  const bool running = a.fixed_shift == 0 || !st.in_reach;
+  video_iter<kQT, true, false>(st, s);
   // (one-armed branches in turn: of an if-else the compiler keeps both arms'
   // accumulators)
-  if (running) {  // the first page once more (its stage is intact), then the rest
-    mfma_drain();
-    // (an opaque zero: 144 registers of constant zeros would be set up ahead of
-    // the segment loop and kept)
-    const float zero = __int_as_float(opaque(0));
-#pragma unroll
-    for (int j = 0; j < kQT; ++j) {
-      st.m[j] = kNegInf;
-      st.l[j] = (f32x4){zero, zero, zero, zero};
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) st.o[dt][j] = (f32x4){zero, zero, zero, zero};
-    }
-    uint32_t stage = stage0;
-    for (int n_valid = valid0;;) {
-      video_page_running_max<kQT>(st, s, stage, n_valid);
-      wait_dma_all_but_last_page();
-      if (s.at == end) break;
-      page_barrier();
-      issue_page(s, s.c);
-      stage = s.stage;
-      n_valid = static_cast<int>(s.valid & 0xffu);
-      stream_advance(s);
-    }
-  }
-  while (s.at < end) video_iter<kQT, false>(st, s);
-  if (!running) video_flush<kQT>(st, s);
+  if (st.any_lazy)
+    while (s.at < end) video_iter<kQT, false, true>(st, s);
+  while (s.at < end) video_iter<kQT, false, false>(st, s);
+  video_flush<kQT>(st, s);
   if (s.at == s.n) wait_dma_all();  // no direct load may still be writing this workgroup's LDS when it exits
 
   // ---- epilogue: lane holds O^T[16 dt + 4 g + r][q] ----

@@ -2,7 +2,7 @@
 (their running maximum is raised as the pages come): each row's result is its
 own, whatever rows share its wave, riders among them; values keep the range
 of fp32; and the rounding of the softmax weights is that of weights taken
-under the row's maximum, not under a bound."""
+under a row's running maximum, not under a bound."""
 import numpy as np
 import pytest
 
@@ -90,29 +90,32 @@ def test_values_keep_their_range(ws, n_q, attained, exponent):
 
 @pytest.mark.parametrize("stretch", [3.0, 4.0, 7.0])
 @pytest.mark.parametrize("n_q,pages", [(120, 20), (240, 80)])
-def test_weights_rounded_under_the_rows_maximum(ws, n_q, pages, stretch):
-    """The distance from the 64-bit result, set against those of the same sums
-    with P rounded to bf16 (a) under each row's own maximum, where the largest
-    weight is exact, and (b) under a shift at a random distance from it: at
-    most halfway between the two."""
+def test_weights_are_rounded_under_a_running_maximum(ws, n_q, pages, stretch):
+    """The distance from the 64-bit result is that of the same sums in 64 bits
+    with P rounded to bf16 under the stated maximum (of the first 32 keys, and
+    raised by every 32 keys that exceed it by more than 8), to 1%: under a
+    shift unrelated to the row's weights it is 1.3% to 4.9% larger where the
+    row maximum reaches 40 to 65, its largest weight being rounded too."""
     rng = np.random.default_rng(int(1000 * stretch) + n_q)
     H, n_keys = 4, 64 * pages
     q, k, v = (synth.normal_bf16(rng, (n, H, 128)) for n in (n_q, n_keys, n_keys))
     q = _bits(stretch * synth.bf16_to_f32(q))
     got = _run(ws, q, k, v)
     qf, kf, vf = bf16_f64(_bits(synth.bf16_to_f32(q) * np.float32(np.log2(np.e) / np.sqrt(128)))), bf16_f64(k), bf16_f64(v)
-    exact, err = np.empty_like(got), {"a": 0.0, "b": 0.0}
+    exact, lazy = np.empty_like(got), np.empty_like(got)
     for h in range(H):
         s = qf[:, h] @ kf[:, h].T
-        s -= s.max(axis=1, keepdims=True)
-        p = np.exp2(s)
+        p = np.exp2(s - s.max(axis=1, keepdims=True))
         exact[:, h] = (p @ vf[:, h]) / p.sum(1, keepdims=True)
-        for name, off in (("a", 0.0), ("b", rng.uniform(0, 1, (n_q, 1)))):
-            pb = bf16_f64(_bits(np.exp2(s - off)))
-            o = bf16_f64(_bits((pb @ vf[:, h]) / pb.sum(1, keepdims=True)))
-            err[name] += ((o - exact[:, h]) ** 2).sum()
-    e = {n: np.sqrt(x / (exact ** 2).sum()) for n, x in err.items()}
-    mine = np.linalg.norm(got - exact) / np.linalg.norm(exact)
-    print(f"stretch {stretch} rows {n_q} pages {pages}: {mine:.6f}, row maximum {e['a']:.6f}, random shift {e['b']:.6f}, "
-          f"share {(mine - e['a']) / (e['b'] - e['a']):.3f}", flush=True)
-    assert mine <= 0.5 * (e["a"] + e["b"])
+        m, o, l = s[:, :32].max(1), 0.0, 0.0
+        for c in range(0, n_keys, 32):
+            top = s[:, c:c + 32].max(1)
+            up = np.where(top > m + 8, top - m, 0.0)
+            m = m + up
+            pb = bf16_f64(_bits(np.exp2(s[:, c:c + 32] - m[:, None])))
+            o = o * np.exp2(-up)[:, None] + pb @ vf[c:c + 32, h]
+            l = l * np.exp2(-up) + pb.sum(1)
+        lazy[:, h] = bf16_f64(_bits(o / l[:, None]))
+    mine, want = (np.linalg.norm(x - exact) / np.linalg.norm(exact) for x in (got, lazy))
+    print(f"stretch {stretch} rows {n_q} pages {pages}: {mine:.6f}, in 64 bits {want:.6f}, {mine / want:.4f}", flush=True)
+    assert abs(mine / want - 1) <= 0.01

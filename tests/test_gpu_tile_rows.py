@@ -1,8 +1,8 @@
 """The video kernel with waves of 64, 48 and 32 rows, against the fp64 oracle:
 row counts whose tiles hold 256, 192 and 128 rows at this head count (and the
 remainders in their last tiles), over partial pages, single keys, streams
-longer than the 128-unit entry window, shifts below the logit bound, and a
-running maximum."""
+longer than the 128-unit entry window, attained logit bounds, and logits far
+below their bound."""
 import numpy as np
 import pytest
 

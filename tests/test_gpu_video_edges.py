@@ -1,8 +1,8 @@
 """The video kernel at the edges of its tiles, its page stream and its softmax
 shift, against the fp64 oracle with the parity gates: subtiles of 16 rows,
 waves of 32 (tiles up to 128 rows) and 64 rows, ragged pages, streams longer
-than the 128-unit entry window, shares that cross several heads, shifts below
-the logit bound, and rows out of a fixed shift's reach."""
+than the 128-unit entry window, shares that cross several heads, and rows under
+a running maximum whose logit bound is attained or far above every logit."""
 import numpy as np
 import pytest
 
@@ -72,9 +72,9 @@ def test_shares_across_heads(ws, H, n_q, n_keys):
 @pytest.mark.parametrize("stretch", [3.0, 5.0, 9.0])
 def test_shift_below_an_attained_bound(ws, n_q, stretch):
     """Each query's dominant key is `stretch` times its own direction: the
-    logit bound (16.3 stretch in log2 units, above 40) is attained, its weight
-    is 2^16 under the lowered shift, and every other weight is below 2^-20 of
-    it, so each row returns its key's V."""
+    logit bound (16.3 stretch in log2 units, above 40) is attained where a row's
+    maximum is raised to it, and every other weight is below 2^-20 of it, so
+    each row returns its key's V."""
     rng = np.random.default_rng(500 + n_q)
     H, n_keys = 2, 64 * 5 + 11
     q, k, v = (synth.normal_bf16(rng, (n, H, 128)) for n in (n_q, n_keys, n_keys))
@@ -94,10 +94,9 @@ def test_shift_below_an_attained_bound(ws, n_q, stretch):
 @pytest.mark.parametrize("n_q,mixed", [(40, False), (200, True)])
 def test_rows_out_of_the_shift_s_reach(ws, n_q, n_keys, mixed):
     """Every key points away from the queries and is 7 times as long: the bound
-    is about 114 in log2 units and every logit about minus that, over 80
-    below the lowered shift, so the range must run under a running maximum
-    (`mixed`: with ordinary rows of a tenth the length in the same waves,
-    which are within reach)."""
+    is about 114 in log2 units and every logit about minus that, so no shift
+    near the bound serves (`mixed`: with ordinary rows of a tenth the length,
+    which have a fixed shift, in the same waves)."""
     rng = np.random.default_rng(600 + n_q + n_keys)
     H = 2
     base = rng.standard_normal((1, H, 128)).astype(np.float32)
