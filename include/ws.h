@@ -325,10 +325,10 @@ typedef struct ws_attn_call {
 
 /* A denoising step's two attentions over the cache (Sec. 3: the long video
  * latent queries and the short audio latent queries of the same unit): the
- * video kernel, the audio kernel, and one launch that merges both calls' key
- * ranges.  Both calls are validated before anything is enqueued.  video,
- * audio: host structs, read before the call returns.  The audio call's key
- * ranges use a workspace of their own.
+ * video kernel, the audio kernel, and one launch that merges the key ranges of
+ * the calls that have any.  Both calls are validated before anything is
+ * enqueued.  video, audio: host structs, read before the call returns.  The
+ * audio call's key ranges use a workspace of their own.
  *
  * Audio rows riding in the video kernel: when the audio call is
  * WS_QUERY_PREPARED, every page the video call sees is visible to the audio

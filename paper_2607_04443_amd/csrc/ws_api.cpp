@@ -430,7 +430,9 @@ int choose_audio_splits(const ws_cache* c, int n_items, int n_pages) {
 // written without a merge.  Measured at 4 to 24 heads and 4 to 20 queries, us
 // per call with ranges and merge / one range: 8 pages 11.6 / 9.1, 12 pages 11.6 /
 // 11.0, 16 pages 11.6 / 12.7 (a wave's pages are a chain: the line lies at three
-// per wave).
+// per wave).  A step whose audio rows do not ride keeps the rule also where its
+// video call merges anyway, though ranges would be 1 (8 pages) to 3 us (12)
+// faster there: the step gives the bits of the separate calls.
 constexpr int kAudioDirectPages = 12;
 
 // The logit scale times log2(e), folded into Q'' (0 selects 1/sqrt(128)).
@@ -448,7 +450,6 @@ struct AttnPlan {
   ws::CombineArgs cb{};
   int splits = 1;  // audio: key ranges; video: workgroup groups
   int64_t part_rows = 0;  // (range, head, query) partial rows the kernel may write
-  int merged_splits = 1, merged_pps = 0;  // audio: the key ranges where a merge follows
 };
 
 ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_t q_head_stride,
@@ -548,8 +549,6 @@ ws_status plan_attention(bool audio, const void* q, int64_t q_tok_stride, int64_
     splits = pps > 0 ? (n_pages + pps - 1) / pps : 1;  // no empty splits
     if (cap < splits) return fail(WS_ERR_SHAPE, "split-KV workspace too small");
     plan->part_rows = static_cast<int64_t>(splits) * H * n_q;
-    plan->merged_splits = splits;
-    plan->merged_pps = pps;
     if (splits == 1 || (c->opt_audio_splits == 0 && n_pages <= kAudioDirectPages)) {
       splits = 1;
       a.audio_direct = 1;
@@ -864,12 +863,6 @@ ws_status step_attention_impl(ws_cache* c, const ws_attn_call* video, const ws_a
   }
   const int64_t room = std::min(c->part_rows, static_workspace ? static_audio_rows(pv) : c->part_rows);
   const bool riders = plan_riders(c, video, audio, pv, pa, room);
-  if (!riders && pv.merge && pa.a.audio_direct) {  // a merge is launched anyway
-    pa.a.audio_direct = 0;
-    pa.a.n_splits = pa.splits = pa.cb.n_splits = pa.merged_splits;
-    pa.a.pages_per_split = pa.merged_pps;
-    pa.merge = true;
-  }
   if (static_workspace)
     if (ws_status st = use_static_workspace(c, pv, pa); st != WS_OK) return st;
   if (riders) {  // the video kernel's ranges of the audio rows follow the audio kernel's
