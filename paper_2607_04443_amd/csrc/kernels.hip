@@ -1625,7 +1625,12 @@ __global__ __launch_bounds__(256, 2) void audio_attn_kernel(const AttnArgs a) {
     for (int w = 0; w < 4; ++w) v += ew[w] * sm_o[w][d0 + k][qi];
     if (k < 4) out0[k] = v * inv; else out1[k - 4] = v * inv;
   }
-  if (a.audio_direct) {  // the only range: what the merge of one range gives
+  if (a.audio_direct) {  // the only range: what the merge of one range gives (a row without weight: zeros)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      out0[k] = l_tot > 0.f ? out0[k] + 0.f : 0.f;  // (+ 0: the merge's sum turns -0 to 0)
+      out1[k] = l_tot > 0.f ? out1[k] + 0.f : 0.f;
+    }
     *reinterpret_cast<u32x4*>(a.out + qq * a.out_tok_stride + head * a.out_head_stride + d0) =
         (u32x4){pack_bf16(out0[0], out0[1]), pack_bf16(out0[2], out0[3]), pack_bf16(out1[0], out1[1]),
                 pack_bf16(out1[2], out1[3])};
