@@ -364,8 +364,9 @@ WS_API ws_status ws_step_attention(ws_cache* cache, const ws_attn_call* video, c
  * head) x H x n_q rows of 260 bytes, audio (key ranges, plus the video
  * kernel's ranges of the audio rows when they ride in it) x H x n_q rows of
  * 516 bytes, each region rounded up to 256 bytes; a larger step returns
- * WS_ERR_SHAPE before anything is enqueued.  (The v0.2 unit at 640x368 with
- * an 8-unit window needs about 29 MB.)  Every call on a device shares that
+ * WS_ERR_SHAPE before anything is enqueued.  (Where room is short, both step
+ * entry points cut the riding rows' own pages into fewer ranges.  The v0.2
+ * unit at 640x368 with an 8-unit window needs about 29 MB.)  Every call on a device shares that
  * device's workspace: calls that overlap in time on one device (different
  * streams, or different threads) race and must be ordered by the caller.
  * Nothing in it has to start at zero: each call writes every partial row it

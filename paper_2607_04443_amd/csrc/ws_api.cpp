@@ -720,15 +720,16 @@ ws_status use_static_workspace(ws_cache* c, AttnPlan& pv, AttnPlan& pa) {
 // latent streams of a unit attend over the same cache; the audio tokens are
 // visible to audio queries only).  When the audio call's visible pages
 // include every page of the video call's, its queries come prepared (Q''),
-// and the spare rows of the video call's last 256-row query tile hold them,
-// the video kernel computes the audio rows over the shared pages while it
-// streams those pages for the video rows, and the audio kernel walks only
-// the pages the video call does not see.  The merge then folds, per (head,
-// row), the audio kernel's ranges and the ranges the video kernel wrote.
-// Fills the fused plans; false (plans untouched) when the step does not
-// qualify.
+// and they fit the spare rows of the video call's last query tile, the video
+// kernel computes the audio rows over the shared pages while it streams those
+// pages for the video rows.  The pages that only the audio rows see go to the
+// last wave of that tile, or to the audio kernel.  The merge then folds, per
+// (head, row), the audio kernel's ranges and the ranges the video kernel wrote.
+// static_rows: audio partial rows that the static workspace holds beside the
+// video call's.  Fills the fused plans; false (plans untouched) when the step
+// does not qualify.
 bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* audio, AttnPlan& pv, AttnPlan& pa,
-                 int64_t room) {
+                 int64_t static_rows) {
   if (c->opt_separate_audio || audio->desc.mode != WS_QUERY_PREPARED) return false;
   if (pv.a.n_classes != 1 || pv.a.cls[0].n_pages == 0) return false;
   const ws::AttnClass& cl = pv.a.cls[0];
@@ -773,8 +774,10 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   // no rows or little to do; otherwise, or when audio key ranges are forced,
   // to the audio kernel.  Each of a head's ranges takes its part of them as a
   // key range of its own, as far as the workspace holds them (`room` partial
-  // rows).
+  // rows): the smaller workspace of the two step entry points, so that both
+  // give the same bits, unless the step does not fit it anyway.
   const int64_t row_set = static_cast<int64_t>(H) * n_rq;
+  const int64_t room = static_rows >= (rmax + 1) * row_set ? std::min(static_rows, c->part_rows) : c->part_rows;
   const bool inline_list = pv.a.pages == nullptr && pv.a.n_pages + n_extra <= ws::AttnArgs::kInlinePages;
   int rx_ranges = 0, splits = 0, pps = 0;
   const int last_rows = rq_row0 + n_rq - (cl.n_qtiles - 1) * cl.tile_rows;
@@ -861,8 +864,7 @@ ws_status step_attention_impl(ws_cache* c, const ws_attn_call* video, const ws_a
     if (ws_status st = plan_video(); st != WS_OK) return st;
     if (c->arena_wraps != wraps + 1) return fail(WS_ERR_SHAPE, "page-list arena too small for one step");
   }
-  const int64_t room = std::min(c->part_rows, static_workspace ? static_audio_rows(pv) : c->part_rows);
-  const bool riders = plan_riders(c, video, audio, pv, pa, room);
+  const bool riders = plan_riders(c, video, audio, pv, pa, static_audio_rows(pv));
   if (static_workspace)
     if (ws_status st = use_static_workspace(c, pv, pa); st != WS_OK) return st;
   if (riders) {  // the video kernel's ranges of the audio rows follow the audio kernel's
