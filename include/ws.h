@@ -339,9 +339,11 @@ typedef struct ws_attn_call {
  * rows over the video call's pages (the pages are streamed once for both); the
  * pages the audio call alone sees (the
  * units' audio tokens) are walked by the last wave of the video kernel's last
- * query tile, or by the audio kernel when the page list does not travel in the
- * kernel arguments, audio key ranges are forced or the workspace is too small;
- * the merge folds all the ranges.
+ * query tile, or by the audio kernel when that wave would take longer over them
+ * than a launch (many such pages for the pages it streams, or, where it has
+ * rows of its own, over 4 such pages per key range or over 16 audio rows), the
+ * page list does not travel in the kernel arguments, audio key ranges are
+ * forced or the workspace is too small; the merge folds all the ranges.
  * WS_OPT_STEP_SEPARATE_AUDIO turns this off.  The video output always equals
  * what ws_unit_attention(video) writes, bit for bit; the audio output equals
  * ws_audio_attention(audio) bit for bit when the rows do not ride, and

@@ -64,6 +64,22 @@ constexpr int kAppendBlocksPerCu = 4;
 constexpr int kRiderPagesPerRange = 4;
 // Pages per range that a wave with rows of its own attends for the rider rows.
 constexpr int kRiderPagesPerBusyWave = 4;
+// What a wave without rows of its own costs the step when it attends the rider
+// rows' own pages, in us: `items` passes of 16 rows over a page, one per two
+// pages of its segment beside the page loads (0.25 each for the loads it holds
+// up), the rest after them (1.05 each, a chain); more than 16 rows make the merge
+// longer.  The audio kernel's launch costs about 7.  Measured, us a step with
+// the pages in the video kernel / in the audio kernel:
+//   12 heads, 920 rows,  2 pages,  4 riders:  5 own pages 16.5 / 20.0,  9  20.4 / 20.8, 20  31.8 / 21.1
+//   12 heads, 920 rows,  8 pages,  4 riders:  9 own pages 22.3 / 24.6, 14  27.7 / 24.9
+//   12 heads, 920 rows,  2 pages, 33 riders:  1 own page  17.2 / 20.3,  3  22.7 / 20.4, 20  76.4 / 21.7
+//   12 heads, 920 rows, 49 pages,  4 riders: 40 own pages 32.6 / 40.5
+//   40 heads, 920 rows, 139 pages, 33 riders: 14 own pages 144.5 / 147.1, 40  195.8 / 161.2
+constexpr double kRiderLaunchUs = 7.0;
+double rider_idle_wave_us(int n_rows, int items, int segment_pages) {
+  const double beside = std::min<double>(items, segment_pages / 2.0);
+  return 0.25 * beside + 1.05 * (items - beside) + (n_rows > ws::kAudioQTile ? 2.5 : 0.0);
+}
 constexpr int kMaxAudioSplits = 512;
 using ws::kMaxAudioQ;
 
@@ -770,9 +786,9 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
                                            ws::video_group_of(part, h0) + 1));
   }
   // The rows' own pages go to the video kernel (its last wave in the last
-  // query tile attends them) when the page list stays inline and that wave has
-  // no rows or little to do; otherwise, or when audio key ranges are forced,
-  // to the audio kernel.  Each of a head's ranges takes its part of them as a
+  // query tile attends them) when the page list stays inline and that takes
+  // less than a launch; otherwise, or when audio key ranges are forced, to the
+  // audio kernel.  Each of a head's ranges takes its part of them as a
   // key range of its own, as far as the workspace holds them (`room` partial
   // rows): the smaller workspace of the two step entry points, so that both
   // give the same bits, unless the step does not fit it anyway.
@@ -786,8 +802,12 @@ bool plan_riders(ws_cache* c, const ws_attn_call* video, const ws_attn_call* aud
   // a time: worth it for one pass over a few pages (about 1 us each) against
   // the audio kernel's launch (6 us).
   const bool few = n_rq <= ws::kAudioQTile && n_extra <= kRiderPagesPerBusyWave * rmax;
-  if (n_extra > 0 && inline_list && c->opt_audio_splits == 0 && (idle_wave || few))
+  if (n_extra > 0 && inline_list && c->opt_audio_splits == 0)
     rx_ranges = static_cast<int>(std::min<int64_t>(std::min(rmax, n_extra), std::max<int64_t>(room / row_set - rmax, 0)));
+  if (rx_ranges > 0) {
+    const int items = (n_rq + ws::kAudioQTile - 1) / ws::kAudioQTile * ((n_extra + rx_ranges - 1) / rx_ranges);
+    if (idle_wave ? rider_idle_wave_us(n_rq, items, cl.n_pages / rmax) > kRiderLaunchUs : !few) rx_ranges = 0;
+  }
   if (n_extra > 0 && rx_ranges == 0) {
     // few pages (latency-bound): as many ranges as give each wave of the
     // audio kernel at most kRiderPagesPerRange / 4 pages

@@ -220,3 +220,25 @@ def test_steps_that_do_not_ride(ws):
         print(assert_gates(bf16_f64(from_dev(oa)), ref, label="RAW audio rows"))
     finally:
         S.close()
+
+
+@pytest.mark.parametrize("n_a,own,where", [
+    (4, 5, "video"), (4, 20, "kernel"),    # a chain of 5 page visits is shorter than a launch, one of 20 is not
+    (33, 1, "video"), (33, 6, "kernel"),   # 33 rows: three visits per page
+])
+def test_many_own_pages_over_few_shared_pages(ws, n_a, own, where):
+    """One wave attends the riders' own pages one after the other, so over two
+    shared pages only a few of them go to the video kernel."""
+    H, n_v = 12, 920
+    S = Step(ws, H, (1, 1), 127, 4, own - 1, 65)
+    try:
+        u = S.unit
+        vmask, amask = (u, u, (synth.KIND_COND,)), (u, 0, (synth.KIND_COND, synth.KIND_AUDIO))
+        qv, qa = S.queries(n_v), S.queries(n_a)
+        fv, fa, rec = S.step(qv, qa, vmask, amask)
+        assert rec[1]["path"] == "audio_riders", rec
+        assert (rec[1]["n_splits"] > 0) == (where == "kernel"), rec
+        np.testing.assert_array_equal(fv, S.separate_video(qv, vmask))
+        assert_gates(bf16_f64(fa), S.oracle(qa, amask), label="riders", bound=S.bound(qa, amask))
+    finally:
+        S.close()
