@@ -399,7 +399,11 @@ constexpr int kMaxAudioQ = 64;  // audio queries per call
 // without room for kAudioQTile rows counts a launch more, one that leaves no
 // idle wave there for those rows' own pages a little more.  A narrower tile
 // is taken only with no more key ranges per head than the widest's, so it
-// never needs more workspace.
+// never needs more workspace, and not where the widest's workgroups take one
+// head each in one round and its own would take several: a second first segment
+// costs more than the launch (24 heads, 2048 rows, 1 page, two heads a workgroup
+// in tiles of 192 / one in tiles of 256: 16.3 / 12.8 us, 23.2 / 18.6 with rows
+// normed in the kernel; a step of 48 heads, 1280 rows, 1 page: 23.3 / 19.6).
 inline int video_max_ranges(int64_t heads, int64_t groups) {
   return !video_heads_split(heads, groups) ? 1
          : static_cast<int>((groups + heads - 1) / heads + 1 > 2 ? (groups + heads - 1) / heads + 1 : 2);
@@ -427,10 +431,12 @@ inline VideoTiling video_tiling(int64_t heads, int64_t n_q, int64_t pages, int64
   VideoTiling best = of(kVideoQTile);
   if (pages == 0 || n_q <= kVideoQTile / 2) return best;
   const int ranges = video_max_ranges(heads, best.groups);
+  const bool head_each = best.groups == heads && heads * ((n_q + kVideoQTile - 1) / kVideoQTile) <= cus;
   double best_us = video_tiling_us(heads, n_q, pages, cus, best);
   for (int rows : {192, 128}) {
     const VideoTiling t = of(rows);
     if (video_max_ranges(heads, t.groups) > ranges) continue;
+    if (head_each && t.groups < heads) continue;
     const double us = video_tiling_us(heads, n_q, pages, cus, t);
     if (us < best_us) {
       best = t;

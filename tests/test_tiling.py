@@ -4,8 +4,8 @@ compiled with the host compiler.
 - video_group_count looks at the counts that can be cheapest only; over a grid
   it picks what a scan of every count picks.
 - A narrower query tile never takes more key ranges per head than the full one
-  (so a call that fits the split-KV workspace still fits), and its waves cover
-  the rows.
+  (so a call that fits the split-KV workspace still fits), nor more heads per
+  workgroup where the full one takes one each, and its waves cover the rows.
 - The picks for the shapes whose times the rule's comment gives."""
 import os
 import subprocess
@@ -58,7 +58,8 @@ int main() {
           const bool known = t.rows == 256 || t.rows == 192 || t.rows == 128;
           if (!known || (q <= 128 && t.rows != 256) || t.groups < 1 ||
               t.groups != ws::video_group_count(h, (q + t.rows - 1) / t.rows, p, cus) ||
-              ws::video_max_ranges(h, t.groups) > ws::video_max_ranges(h, wide)) {
+              ws::video_max_ranges(h, t.groups) > ws::video_max_ranges(h, wide) ||
+              (wide == h && h * ((q + 255) / 256) <= cus && t.groups < h)) {
             std::printf("FAIL tiling h=%d q=%d p=%d cus=%d rows=%d groups=%lld\n", h, q, p, cus, t.rows, (long long)t.groups);
             return 1;
           }
@@ -69,7 +70,8 @@ int main() {
         }
   struct { int h, q, p, rows, groups; } pinned[] = {{12, 252, 13, 192, 84}, {40, 920, 19, 192, 40}, {17, 333, 38, 128, 85},
                                                     {40, 920, 49, 192, 40}, {40, 920, 139, 256, 64}, {40, 920, 479, 256, 64},
-                                                    {3, 129, 5, 128, 3}, {3, 250, 5, 192, 3}, {3, 500, 5, 192, 3}, {3, 380, 5, 256, 3}, {3, 300, 5, 128, 3}};
+                                                    {3, 129, 5, 128, 3}, {3, 250, 5, 192, 3}, {3, 500, 5, 192, 3}, {3, 380, 5, 256, 3}, {3, 300, 5, 128, 3},
+                                                    {24, 2048, 1, 256, 24}, {28, 1784, 2, 256, 28}, {64, 1024, 2, 256, 64}, {46, 1016, 2, 256, 46}};
   for (auto& c : pinned) {
     const ws::VideoTiling t = ws::video_tiling(c.h, c.q, c.p, 256);
     if (t.rows != c.rows) { std::printf("FAIL pinned h=%d q=%d p=%d: %d\n", c.h, c.q, c.p, t.rows); return 1; }
