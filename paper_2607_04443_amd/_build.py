@@ -59,7 +59,7 @@ def build(verbose=False):
         objs.append(obj)
     host_tmp = HOST_LIB_PATH + ".tmp"
     host_cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-                "-I", CSRC, os.path.join(CSRC, "pagetable.cpp"),
+                "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", CSRC, os.path.join(CSRC, "pagetable.cpp"),
                 os.path.join(CSRC, "pagetable_capi.cpp"), "-o", host_tmp]
     jobs.append(host_cmd)
     with ThreadPoolExecutor(max_workers=4) as ex:

@@ -1,8 +1,9 @@
-// Host-only C entry points over the page table, for CPU tests of the cache
-// bookkeeping (built into libws_host.so with g++; no HIP involved).
+// Host-only C entry points over the page table and the video kernel's tiling
+// rule, for tests (built into libws_host.so with g++; no HIP call involved).
 #include <cstdint>
 
 #include "pagetable.hpp"
+#include "ws_kernels.hpp"
 
 #define WSH_API extern "C" __attribute__((visibility("default")))
 
@@ -63,4 +64,9 @@ WSH_API int32_t wsh_segment_pages(void* pt, int32_t unit, int32_t kind, int32_t*
   for (int32_t i = 0; i < cap && i < static_cast<int32_t>(s->pages.size()); ++i)
     pages[i] = s->pages[static_cast<size_t>(i)];
   return static_cast<int32_t>(s->pages.size());
+}
+
+// Rows per query tile that the video kernel takes for a call's rows of one unit.
+WSH_API int32_t wsh_video_tile_rows(int32_t heads, int32_t n_q, int32_t pages, int32_t cus) {
+  return ws::video_tiling(heads, n_q, pages, cus).rows;
 }

@@ -1,6 +1,8 @@
 """Shared helpers of the GPU parity tests: load a seeded workload into both
 the HIP cache (through the C ABI binding) and the oracle's logical cache, and
 compare outputs against the oracle with the parity gates."""
+import ctypes
+
 import numpy as np
 
 import oracle
@@ -53,6 +55,19 @@ def dev_i32(a):
 def dev_f32(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def video_waves(heads, n_q, pages, splits=0, riders=0):
+    """What a video call of one unit runs on this device: rows per query tile,
+    rows per wave of its last tile, and that tile's waves without rows."""
+    import torch
+    from paper_2607_04443_amd import _build
+    cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+    # (forced key ranges keep the full tile)
+    tile = 256 if splits else ctypes.CDLL(_build.HOST_LIB_PATH).wsh_video_tile_rows(heads, n_q, pages, cus)
+    last = n_q + riders - (-(-n_q // tile) - 1) * tile
+    wave = tile // 4 if last > 128 else 32
+    return tile, wave, 4 - -(-last // wave)
 
 
 class Loaded:

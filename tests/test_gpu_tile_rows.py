@@ -1,8 +1,7 @@
-"""The video kernel with waves of 64, 48 and 32 rows, against the fp64 oracle:
-row counts whose tiles hold 256, 192 and 128 rows at this head count (and the
-remainders in their last tiles), over partial pages, single keys, streams
-longer than the 128-unit entry window, attained logit bounds, and logits far
-below their bound."""
+"""The video kernel in query tiles of 256, 192 and 128 rows (waves of 64, 48 and
+32), against the fp64 oracle: whole tiles and the remainders in their last ones,
+over partial pages, single keys, streams longer than the 128-unit entry
+window, and logits far below their bound.  Each case states its tile."""
 import numpy as np
 import pytest
 
@@ -10,8 +9,9 @@ from paper_2607_04443_amd import synth
 import test_gpu_video_edges as edges
 
 pytestmark = pytest.mark.gpu
-# three heads: 380 rows take tiles of 256 rows, 250 and 500 of 192, 300 of 128
-ROWS = [380, 250, 500, 300]
+# three heads, one to six pages: rows per query tile
+TILE = {380: 256, 250: 192, 500: 192, 300: 128}
+ROWS = list(TILE)
 
 
 def _bits(seed, n_q, n_keys, H=3):
@@ -22,23 +22,21 @@ def _bits(seed, n_q, n_keys, H=3):
 @pytest.mark.parametrize("n_q", ROWS)
 @pytest.mark.parametrize("n_keys", [1, 33, 63, 64, 65, 64 * 4, 64 * 5 + 7])
 def test_key_counts(ws, n_q, n_keys):
-    edges._check(ws, *_bits(n_q + n_keys, n_q, n_keys), label=f"{n_q} rows, {n_keys} keys")
+    edges._check(ws, *_bits(n_q + n_keys, n_q, n_keys), label=f"{n_q} rows, {n_keys} keys", tile=TILE[n_q])
 
 
-@pytest.mark.parametrize("n_q", [250, 500])
-def test_long_streams(ws, n_q):
-    # 64 heads x 20 pages over two or three tiles: shares of several heads, streams past 128 units
-    edges._check(ws, *_bits(n_q, n_q, 64 * 20 - 9, H=64), label=f"{n_q} rows, shares across heads")
-    edges._check(ws, *_bits(n_q, n_q, 64 * 1000 - 23, H=1), label=f"{n_q} rows, a long stream")
-
-
-@pytest.mark.parametrize("n_q", [250, 380])
-@pytest.mark.parametrize("stretch", [3.0, 9.0])
-def test_lowered_shift(ws, n_q, stretch):
-    edges.test_shift_below_an_attained_bound(ws, n_q, stretch)
+# shares of several heads (64 groups of 20 and 10 units), then streams of 143
+# units (one of 1900 rows: every 31st row compared, for the oracle's time)
+@pytest.mark.parametrize("H,n_q,pages,tile,every", [(64, 250, 20, 128, 1), (64, 500, 20, 192, 1), (64, 500, 10, 192, 1),
+                                                    (1, 250, 1000, 128, 1), (1, 500, 1000, 128, 1),
+                                                    (3, 1900, 1000, 192, 31)])
+def test_long_streams(ws, H, n_q, pages, tile, every):
+    edges._check(ws, *_bits(n_q, n_q, 64 * pages - 9, H=H), label=f"{H} heads, {n_q} rows, {pages} pages", tile=tile,
+                 every=every)
 
 
 @pytest.mark.parametrize("n_keys", [1, 64 * 3 + 24])
 @pytest.mark.parametrize("n_q", ROWS)
 def test_running_maximum(ws, n_q, n_keys):
-    edges.test_rows_out_of_the_shift_s_reach(ws, n_q, n_keys, n_q == 250)
+    # (two heads take the same tiles)
+    edges.test_rows_out_of_the_shift_s_reach(ws, n_q, 0, TILE[n_q], n_keys, n_q == 250)
