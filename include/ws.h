@@ -259,7 +259,8 @@ WS_API ws_status ws_kv_release(ws_cache* cache, int32_t unit, ws_kind kind);
  *   out[i] = sum_j softmax_j(scale * <Q'_i, K'_j>) V_j over the visible keys.
  *   q:   device bf16 [n_q][H][128] with strides (q_tok_stride, q_head_stride).
  *   out: device bf16 [n_q][H][128] with strides (out_tok_stride, out_head_stride).
- * 1 <= n_q <= max_q_tokens.  MFMA flash kernel: 256-query tiles, 64-key pages.
+ * 1 <= n_q <= max_q_tokens.  MFMA flash kernel: query tiles of 256, 192 or 128
+ * rows (chosen from heads, rows and pages; 256 with forced ranges), 64-key pages.
  * Groups of workgroups (one per query tile) take even shares of the
  * (head, page) work, so a head's keys may be split into ranges (split-KV);
  * those are merged by log-sum-exp in a second kernel.

@@ -30,12 +30,9 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kNegInf = -__builtin_inff();
 // Largest logit bound (log2 units) used as a fixed softmax shift.
@@ -132,14 +129,7 @@ __device__ __forceinline__ void clamp_pos(const RopeTables& r, int t, int h, int
 // Loads a token's (t, h, w), clamped into the table; flags a clamp.
 __device__ __forceinline__ void load_pos(const RopeTables& r, const int32_t* positions, int tok,
                                          uint32_t* flags, int& pt, int& ph, int& pw) {
-  int t = positions[3 * tok + 0], h = positions[3 * tok + 1], w = positions[3 * tok + 2];
-  const int ct = min(max(t, 0), r.max_pos[0] - 1);
-  const int ch = min(max(h, 0), r.max_pos[1] - 1);
-  const int cw = min(max(w, 0), r.max_pos[2] - 1);
-  if ((ct != t) | (ch != h) | (cw != w)) atomicOr(flags, kFlagPositionClamped);
-  pt = ct;
-  ph = ch;
-  pw = cw;
+  clamp_pos(r, positions[3 * tok + 0], positions[3 * tok + 1], positions[3 * tok + 2], flags, pt, ph, pw);
 }
 
 typedef const __attribute__((address_space(4))) AppendSeg* const_append_seg;
@@ -402,9 +392,9 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const AppendArgs args) {
 }
 
 // ------------------------------------------------------------------------- //
-// unit_attn (video): 256-query tiles on 4 waves (one per SIMD) of 64 queries,
-// or of 32 queries where a tile holds at most 128 rows; 64-key pages through
-// LDS.
+// unit_attn (video): query tiles of 256, 192 or 128 rows on 4 waves (one per
+// SIMD) of 64, 48 or 32 queries, a last tile of at most 128 rows on waves of
+// 32; 64-key pages through LDS.
 //
 // Per wave and page, with lane l = 16 g + i (i = query column of a 16-query
 // subtile, g = lane group) and v_mfma_f32_16x16x32_bf16:
@@ -1877,8 +1867,9 @@ __device__ __forceinline__ void unit_attn(const AttnArgs& a) {
   s.lo = static_cast<int>(part_group_lo(w.part, group));
   s.n = static_cast<int>(part_group_lo(w.part, group + 1)) - s.lo;
   if (s.n == 0) return;
-  // the list entries of the window are requested here and combined after the
-  // queries' loads are under way
+  // the list entries of the window are under way while the lane's offsets are
+  // computed; stream_start waits for them, and the first segment's queries are
+  // loaded behind the direct loads it issues
   stream_request(s);
   {
     // K block wave: row 4 wave + lane / 16 of key tile 0, position lane % 16

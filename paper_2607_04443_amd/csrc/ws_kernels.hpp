@@ -298,9 +298,9 @@ struct CombineArgs {
 
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t stream, hipEvent_t start = nullptr,
                             hipEvent_t stop = nullptr);
-// Video path: 256-query tiles on 4 waves, 16x16x32 bf16 MFMA, LDS-staged
-// pages; n_groups x n_qtiles workgroups, each with an even share of the
-// (head, page) units.
+// Video path: query tiles of 256, 192 or 128 rows on 4 waves, 16x16x32 bf16
+// MFMA, LDS-staged pages; n_groups x n_qtiles workgroups per class, each with
+// an even share of the (head, page) units.
 hipError_t launch_unit_attention(const AttnArgs& a, hipStream_t stream, hipEvent_t start = nullptr,
                                  hipEvent_t stop = nullptr);
 // Audio path: 4 independent waves per (head, 16-query tile, key range),
