@@ -23,7 +23,8 @@ HIP_SOURCES = ["kernels.hip", "peaks.hip", "ws_api.cpp", "pagetable.cpp", "block
 LINK_FLAGS = ["-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lhipblaslt"]
 # Packed fp32 ops are kept out of the generated code on purpose.  The kernels
 # never form NaNs from finite inputs (masked logits are -inf, and no -inf - -inf
-# is evaluated), so NaN-quieting canonicalisations are not needed.
+# is evaluated; a row of zeros normed with eps = 0 aside, whose norm has no
+# value), so NaN-quieting canonicalisations are not needed.
 # The MFMA builtins are to write vector registers: next to the video kernel's
 # accumulation-register O (inline asm) the compiler would otherwise put its S
 # tiles there too and copy every logit out before its exponential.
