@@ -35,6 +35,12 @@ def test_long_streams(ws, H, n_q, pages, tile, every):
                  every=every)
 
 
+@pytest.mark.parametrize("n_q", [250, 300, 380])
+@pytest.mark.parametrize("stretch", [3.0, 9.0])
+def test_attained_bounds(ws, n_q, stretch):
+    edges.test_shift_below_an_attained_bound(ws, n_q, 0, TILE[n_q], stretch, False)
+
+
 @pytest.mark.parametrize("n_keys", [1, 64 * 3 + 24])
 @pytest.mark.parametrize("n_q", ROWS)
 def test_running_maximum(ws, n_q, n_keys):
